@@ -96,8 +96,9 @@ __device__ __forceinline__ void butterfly(int k, float2 e, float2 o, float2& x, 
   y = make_float2(fmaf(2.0f, e.x, -r.x), fmaf(2.0f, e.y, -r.y));
 }
 
-// In-register DFT of size R (power of two <= 16) by radix-2 decimation in time.
-template <int R, bool INV>
+// In-register DFT of size R (power of two <= 16) by radix-2 decimation in time. PAIRED: the first
+// level's sums and differences of (x[i], x[i + R/2]) are already in place.
+template <int R, bool INV, bool PAIRED = false>
 struct Dft {
   __device__ __forceinline__ static void run(float2* x) {
     float2 e[R / 2], o[R / 2];
@@ -106,15 +107,67 @@ struct Dft {
       e[i] = x[2 * i];
       o[i] = x[2 * i + 1];
     }
-    Dft<R / 2, INV>::run(e);
-    Dft<R / 2, INV>::run(o);
+    Dft<R / 2, INV, PAIRED>::run(e);
+    Dft<R / 2, INV, PAIRED>::run(o);
 #pragma unroll
     for (int k = 0; k < R / 2; ++k) butterfly<R, INV>(k, e[k], o[k], x[k], x[k + R / 2]);
   }
 };
 template <bool INV>
-struct Dft<1, INV> {
+struct Dft<2, INV, true> {
   __device__ __forceinline__ static void run(float2*) {}
+};
+template <bool INV>
+struct Dft<1, INV, false> {
+  __device__ __forceinline__ static void run(float2*) {}
+};
+
+// Radix-2 butterfly with a twiddle held in registers, W = t (conj t inverse), or W = -i t (its
+// conjugate inverse) with ROT: six instructions.
+template <bool INV, bool ROT>
+__device__ __forceinline__ void butterfly_tw(float2 t, float2 e, float2 o, float2& x, float2& y) {
+  const float ty = INV ? -t.y : t.y;
+  float2 r;
+  if constexpr (!ROT)
+    r = make_float2(fmaf(-ty, o.y, fmaf(t.x, o.x, e.x)), fmaf(t.x, o.y, fmaf(ty, o.x, e.y)));
+  else if constexpr (INV)  // +i conj(t) o
+    r = make_float2(fmaf(-t.x, o.y, fmaf(-ty, o.x, e.x)), fmaf(-ty, o.y, fmaf(t.x, o.x, e.y)));
+  else  // -i t o
+    r = make_float2(fmaf(t.x, o.y, fmaf(ty, o.x, e.x)), fmaf(ty, o.y, fmaf(-t.x, o.x, e.y)));
+  x = r;
+  y = make_float2(fmaf(2.0f, e.x, -r.x), fmaf(2.0f, e.y, -r.y));
+}
+
+// DFT of size R of x[r] w^r (conj w inverse). The twiddle goes into the butterflies: level Q
+// (2, 4, ..., R) multiplies by w^{R/Q} exp(-2 pi i k / Q), k < Q/2, and the upper half of those is
+// -i times the lower half, so R/2 register twiddles serve all levels (w holds level Q's from
+// index Q/4 on, level 2's at 0) and no separate multiplications are left: 192 VALU instructions
+// for R = 16 instead of 208, 16 twiddle registers instead of 30.
+template <int R, bool INV>
+struct DftTw {
+  __device__ __forceinline__ static void run(float2* x, const float2* w) {
+    float2 e[R / 2], o[R / 2];
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) {
+      e[i] = x[2 * i];
+      o[i] = x[2 * i + 1];
+    }
+    DftTw<R / 2, INV>::run(e, w);
+    DftTw<R / 2, INV>::run(o, w);
+    if constexpr (R == 2) {
+      butterfly_tw<INV, false>(w[0], e[0], o[0], x[0], x[1]);
+    } else {
+#pragma unroll
+      for (int k = 0; k < R / 4; ++k) {
+        butterfly_tw<INV, false>(w[R / 4 + k], e[k], o[k], x[k], x[k + R / 2]);
+        butterfly_tw<INV, true>(w[R / 4 + k], e[k + R / 4], o[k + R / 4], x[k + R / 4], x[k + 3 * R / 4]);
+      }
+    }
+  }
+};
+template <bool INV>
+struct DftTw<1, INV> {
+  __device__ __forceinline__ static void run(float2*, const float2*) {}
 };
 
 // LDS slot of element i of an exchange written by a pass of span LW. On gfx950 a wave's float2
@@ -140,45 +193,99 @@ __device__ __forceinline__ int lds_slot(int i) {
 // LDS float2 slots of a segment of S points under every padding above.
 template <int S>
 constexpr int lds_slots() { return S + S / 8; }
+// Whether a variant's template loop runs the two phases one stage apart (one wave per workgroup,
+// registers for two phases), and the LDS float2 slots of a workgroup (an exchange buffer per phase then).
+template <int S, int E, int R4>
+constexpr bool piped() { return S / E == 64 && E == 16 && R4 == 1; }
+// Waves per SIMD a piped kernel's registers must leave room for: a SIMD issues the VALU instructions
+// of two waves side by side, of one wave alone only every fourth cycle.
+template <int S, int E, int R4>
+constexpr int min_waves() { return piped<S, E, R4>() ? 2 : 1; }
+template <int S, int E, int R4>
+constexpr int lds_total() { return piped<S, E, R4>() ? 2 * lds_slots<S>() : lds_slots<S>(); }
 
-// One Stockham pass. The thread owns butterflies b = tid + m * TPB, m < E / R.
-// tw: table of exp(-2 pi i k / S), k < S. RP: radix of the pass that wrote the
-// LDS exchange this pass reads (FROM_LDS), whose span was L / RP.
+// One Stockham pass in its three parts. The thread owns butterflies b = tid + m * TPB, m < E / R.
+// LW: span of the pass that wrote the LDS exchange that is read.
+template <int S, int E, int R, int LW>
+__device__ __forceinline__ void exchange_read(float2 (&v)[E], const float2* lds, int tid) {
+  constexpr int TPB = S / E;
+#pragma unroll
+  for (int m = 0; m < E / R; ++m) {
+    const int b = tid + m * TPB;
+#pragma unroll
+    for (int r = 0; r < R; ++r) v[m * R + r] = lds[lds_slot<LW>(b + r * (S / R))];
+  }
+}
+// L: span of the pass that writes.
+template <int S, int E, int R, int L>
+__device__ __forceinline__ void exchange_write(const float2 (&v)[E], float2* lds, int tid) {
+  constexpr int TPB = S / E;
+#pragma unroll
+  for (int m = 0; m < E / R; ++m) {
+    const int b = tid + m * TPB;
+    const int j = b % L;
+#pragma unroll
+    for (int k = 0; k < R; ++k) lds[lds_slot<L>((b - j) * R + j + L * k)] = v[m * R + k];
+  }
+}
+// Register twiddles of the pass's butterflies (DftTw), R/2 for each: level Q holds
+// exp(-2 pi i (j + k L) / (L Q)), k < max(1, Q/4), j = b mod L. tw: table of exp(-2 pi i k / S).
+template <int S, int E, int R, int L>
+__device__ __forceinline__ void load_twiddles(float2 (&w)[E / 2], const float2* __restrict__ tw, int tid) {
+  constexpr int TPB = S / E;
+#pragma unroll
+  for (int m = 0; m < E / R; ++m) {
+    const int j = (tid + m * TPB) % L;
+#pragma unroll
+    for (int q = 0; q < R / 2; ++q) {
+      const int Q = q == 0 ? 2 : q == 1 ? 4 : q < 4 ? 8 : 16;  // level of slot q
+      const int k = q == 0 ? 0 : q - Q / 4;
+      w[m * (R / 2) + q] = tw[((j + k * L) * (S / (L * Q))) & (S - 1)];
+    }
+  }
+}
+// The radix-R DFTs with their twiddles (L > 1).
+template <int E, int R, int L, bool INV>
+__device__ __forceinline__ void pass_compute(float2 (&v)[E], const float2 (&w)[E / 2]) {
+#pragma unroll
+  for (int m = 0; m < E / R; ++m) {
+    if constexpr (L > 1) DftTw<R, INV>::run(&v[m * R], &w[m * (R / 2)]);
+    else Dft<R, INV>::run(&v[m * R]);
+  }
+}
+// First inverse pass of F times a template spectrum h: the products go into the DFT's first level
+// (10 VALU instructions a pair instead of 12).
+template <int E, int R>
+__device__ __forceinline__ void product_pass(float2 (&v)[E], const float2 (&F)[E], const float2 (&h)[E]) {
+#pragma unroll
+  for (int m = 0; m < E / R; ++m) {
+#pragma unroll
+    for (int i = 0; i < R / 2; ++i) {
+      const float2 a = F[m * R + i], b = h[m * R + i];
+      const float2 f = F[m * R + i + R / 2], g = h[m * R + i + R / 2];
+      const float2 e = make_float2(fmaf(-a.y, b.y, a.x * b.x), fmaf(a.y, b.x, a.x * b.y));
+      const float2 s = make_float2(fmaf(f.x, g.x, fmaf(-f.y, g.y, e.x)), fmaf(f.x, g.y, fmaf(f.y, g.x, e.y)));
+      v[m * R + i] = s;
+      v[m * R + i + R / 2] = make_float2(fmaf(2.0f, e.x, -s.x), fmaf(2.0f, e.y, -s.y));
+    }
+    Dft<R, true, true>::run(&v[m * R]);
+  }
+}
+
+// One whole Stockham pass, exchanges ordered by workgroup barriers. RP: radix of the pass that
+// wrote the LDS exchange this pass reads (FROM_LDS), whose span was L / RP.
 template <int S, int E, int R, int L, bool INV, bool FROM_LDS, bool TO_LDS, int RP = 1>
 __device__ __forceinline__ void stockham_pass(float2 (&v)[E], float2* lds, const float2* __restrict__ tw,
                                               int tid) {
-  constexpr int TPB = S / E;
-  constexpr int M = E / R;
   if constexpr (FROM_LDS) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int b = tid + m * TPB;
-#pragma unroll
-      for (int r = 0; r < R; ++r) v[m * R + r] = lds[lds_slot<L / RP>(b + r * (S / R))];
-    }
+    exchange_read<S, E, R, L / RP>(v, lds, tid);
     __syncthreads();
   }
-#pragma unroll
-  for (int m = 0; m < M; ++m) {
-    const int b = tid + m * TPB;
-    if constexpr (L > 1) {
-      const int j = b % L;
-#pragma unroll
-      for (int r = 1; r < R; ++r) {
-        const float2 w = tw[(r * j * (S / (L * R))) & (S - 1)];
-        v[m * R + r] = INV ? cmulc(v[m * R + r], w) : cmul(v[m * R + r], w);
-      }
-    }
-    Dft<R, INV>::run(&v[m * R]);
-  }
+  float2 w[E / 2];
+  if constexpr (L > 1) load_twiddles<S, E, R, L>(w, tw, tid);
+  pass_compute<E, R, L, INV>(v, w);
   if constexpr (TO_LDS) {
-#pragma unroll
-    for (int m = 0; m < M; ++m) {
-      const int b = tid + m * TPB;
-      const int j = b % L;
-#pragma unroll
-      for (int k = 0; k < R; ++k) lds[lds_slot<L>((b - j) * R + j + L * k)] = v[m * R + k];
-    }
+    exchange_write<S, E, R, L>(v, lds, tid);
     __syncthreads();
   }
 }
@@ -475,95 +582,179 @@ __device__ __forceinline__ void fft_tile(const FftJob& j, int64_t seg, int m0, i
 #pragma unroll
   for (int e = 0; e < E; ++e) F[e] = v[e];
 
-  // ---- template loop ----
   // lags kept by this segment: lag < U and k0 = seg U + lag < nbins
   const int lag_lim = (int)min((int64_t)U, j.nbins - seg * U);
-  for (int mm = m0; mm < m1; ++mm) {
-    const int t = TABLE ? ((gci32_ptr)j.members)[mm] : j.members[mm];
-    const int64_t row = j.row_by_member ? (int64_t)(mm - j.row_base) : (int64_t)(t - j.t_begin);
-    float P0[E];
+  // spectrum of one phase of member mm: bins b + k S / RL of this thread, in the order of F
+  // (the job's fields are read once, here: inside the loop their scalar loads would share a wait
+  // counter with the LDS traffic)
+  const float2* const bank = j.bank_fft;
+  const int row_by_member = j.row_by_member, row_base = j.row_base, t_begin = j.t_begin;
+  float* const plane = j.plane;
+  const int64_t ld = j.ld, rmax_ld = j.rmax_ld;
+  uint64_t* const row_max = j.row_max;
+  auto load_h = [&](float2(&h)[E], int mm, int phase) {
+    const float2* __restrict__ H = bank + ((int64_t)mm * 2 + phase) * S;
+    const gcf2_ptr Hg = (gcf2_ptr)bank + ((int64_t)mm * 2 + phase) * S;  // TABLE
 #pragma unroll
-    for (int phase = 0; phase < 2; ++phase) {
-      const float2* __restrict__ H = j.bank_fft + ((int64_t)mm * 2 + phase) * S;
-      const gcf2_ptr Hg = (gcf2_ptr)j.bank_fft + ((int64_t)mm * 2 + phase) * S;  // TABLE
-      {
-        constexpr int M = E / RL;
+    for (int m = 0; m < E / RL; ++m) {
+      const unsigned b = tid + m * TPB;
 #pragma unroll
-        for (int m = 0; m < M; ++m) {
-          const unsigned b = tid + m * TPB;
+      for (int k = 0; k < RL; ++k) h[m * RL + k] = TABLE ? gload(Hg + b + k * (S / RL)) : H[b + k * (S / RL)];
+    }
+  };
+  auto row_of = [&](int mm, int t) -> int64_t {
+    return row_by_member ? (int64_t)(mm - row_base) : (int64_t)(t - t_begin);
+  };
+  // Results of one template: P0 the powers of phase 0 and v the correlations of phase 1; the
+  // thread holds lag b + k S/R1 in element m R1 + k.
+  auto emit = [&](int mm, int t, const float(&P0)[E], const float2(&v)[E]) {
+    const int64_t row = row_of(mm, t);
+    if constexpr (CAND > 0) {
+      float P1[E];
 #pragma unroll
-          for (int k = 0; k < RL; ++k) v[m * RL + k] = cmul(F[m * RL + k], TABLE ? gload(Hg + b + k * (S / RL)) : H[b + k * (S / RL)]);
-        }
-      }
-      if constexpr (P4) {
-        stockham_pass<S, E, R4, 1, true, false, true>(v, lds, tw, tid);
-        stockham_pass<S, E, R3, R4, true, true, true, R4>(v, lds, tw, tid);
-        stockham_pass<S, E, R2, R4 * R3, true, true, true, R3>(v, lds, tw, tid);
-        stockham_pass<S, E, R1, R4 * R3 * R2, true, true, false, R2>(v, lds, tw, tid);
-      } else {
-        stockham_pass<S, E, R3, 1, true, false, true>(v, lds, tw, tid);
-        stockham_pass<S, E, R2, R3, true, true, true, R3>(v, lds, tw, tid);
-        stockham_pass<S, E, R1, R3 * R2, true, true, false, R2>(v, lds, tw, tid);
-      }
-      // thread holds lag b + k S/R1 in v[m R1 + k]
-      if (phase == 0) {
+      for (int e = 0; e < E; ++e) P1[e] = fmaf(v[e].x, v[e].x, v[e].y * v[e].y);
+      cand_epilogue<S, E, R1, CAND>(*ca, j, seg, U, lag_lim, row, (int64_t)(m0 - row_base), t, P0, P1, xch, wsum,
+                                    n_hit, tid);
+    } else {
+      constexpr int M = E / R1;
+      // KEYS: this lane's best power bits and 2c + phase of the column c holding it; columns
+      // are visited in increasing lag order and only a strictly larger power replaces the
+      // best, so equal powers keep the lowest plane index (the order of peak_key)
+      [[maybe_unused]] uint32_t bb = 0;
+      [[maybe_unused]] int bc = -1;
+      // uniform row base; lanes add 32-bit offsets (through a global view: the job may come from
+      // a device-side table)
+      const bool out2 = plane != nullptr;
+      const gf2_ptr out2g = out2 ? (gf2_ptr)(plane + row * ld) + seg * U : nullptr;
 #pragma unroll
-        for (int e = 0; e < E; ++e) P0[e] = fmaf(v[e].x, v[e].x, v[e].y * v[e].y);
-      } else if constexpr (CAND > 0) {
-        float P1[E];
-#pragma unroll
-        for (int e = 0; e < E; ++e) P1[e] = fmaf(v[e].x, v[e].x, v[e].y * v[e].y);
-        cand_epilogue<S, E, R1, CAND>(*ca, j, seg, U, lag_lim, row, (int64_t)(m0 - j.row_base), t, P0, P1, xch,
-                                      wsum, n_hit, tid);
-      } else {
-        constexpr int M = E / R1;
-        // KEYS: this lane's best power bits and 2c + phase of the column c holding it; columns
-        // are visited in increasing lag order and only a strictly larger power replaces the
-        // best, so equal powers keep the lowest plane index (the order of peak_key)
-        [[maybe_unused]] uint32_t bb = 0;
-        [[maybe_unused]] int bc = -1;
-        // uniform row base; lanes add 32-bit offsets (through a global view: the job may come from
-        // a device-side table)
-        const bool out2 = j.plane != nullptr;
-        const gf2_ptr out2g = j.plane ? (gf2_ptr)(j.plane + row * j.ld) + seg * U : nullptr;
-#pragma unroll
-        for (int i = 0; i < E; ++i) {
-          // column c holds lag tid + c TPB in v[(c mod M) R1 + c / M]; KEYS visits the columns
-          // in order, the plane alone in register order
-          const int e = KEYS ? (i % M) * R1 + i / M : i;
-          const int c = KEYS ? i : i / R1 + (i % R1) * M;
-          const int lag = tid + c * TPB;
-          if (lag < lag_lim) {
-            const float2 vv = v[e];
-            const float p0 = P0[e];
-            const float p1 = fmaf(vv.x, vv.x, vv.y * vv.y);
-            // plane points are written once and never read here: non-temporal stores keep
-            // them from displacing the template spectra and segments in the caches
-            if (out2) __builtin_nontemporal_store(f2vec{p0, p1}, &out2g[(unsigned)lag]);
-            if constexpr (KEYS) {
-              const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
-              if (c == 0 || u0 > bb) {
-                bb = u0;
-                bc = 2 * c;
-              }
-              if (u1 > bb) {
-                bb = u1;
-                bc = 2 * c + 1;
-              }
+      for (int i = 0; i < E; ++i) {
+        // column c holds lag tid + c TPB in v[(c mod M) R1 + c / M]; KEYS visits the columns
+        // in order, the plane alone in register order
+        const int e = KEYS ? (i % M) * R1 + i / M : i;
+        const int c = KEYS ? i : i / R1 + (i % R1) * M;
+        const int lag = tid + c * TPB;
+        if (lag < lag_lim) {
+          const float2 vv = v[e];
+          const float p0 = P0[e];
+          const float p1 = fmaf(vv.x, vv.x, vv.y * vv.y);
+          // plane points are written once and never read here: non-temporal stores keep
+          // them from displacing the template spectra and segments in the caches
+          if (out2) __builtin_nontemporal_store(f2vec{p0, p1}, &out2g[(unsigned)lag]);
+          if constexpr (KEYS) {
+            const uint32_t u0 = __float_as_uint(p0), u1 = __float_as_uint(p1);
+            if (c == 0 || u0 > bb) {
+              bb = u0;
+              bc = 2 * c;
+            }
+            if (u1 > bb) {
+              bb = u1;
+              bc = 2 * c + 1;
             }
           }
         }
-        [[maybe_unused]] uint64_t best = 0;
-        if constexpr (KEYS) {
-          if (bc >= 0) {
-            const int64_t p = 2 * (seg * U + tid) + (int64_t)(bc >> 1) * (2 * TPB) + (bc & 1);
-            best = peak_key(__uint_as_float(bb), p);
-          }
-          best = block_max_key<TPB>(best, red);
-          if (tid == 0) {
-            if (j.rmax_ld == 0) atomicMax(reinterpret_cast<unsigned long long*>(j.row_max + row), (unsigned long long)best);
-            else j.row_max[row * j.rmax_ld + seg] = best;
-          }
+      }
+      [[maybe_unused]] uint64_t best = 0;
+      if constexpr (KEYS) {
+        if (bc >= 0) {
+          const int64_t p = 2 * (seg * U + tid) + (int64_t)(bc >> 1) * (2 * TPB) + (bc & 1);
+          best = peak_key(__uint_as_float(bb), p);
+        }
+        best = block_max_key<TPB>(best, red);
+        if (tid == 0) {
+          if (rmax_ld == 0) atomicMax(reinterpret_cast<unsigned long long*>(row_max + row), (unsigned long long)best);
+          else row_max[row * rmax_ld + seg] = best;
+        }
+      }
+    }
+  };
+
+  // ---- template loop ----
+  if constexpr (piped<S, E, R4>()) {
+    // One wave per workgroup: a wave's LDS instructions execute in the order it issues them, so
+    // its exchanges need no barrier and no wait for the stores, only an order the compiler keeps.
+    // The two phases run one stage apart, each with its own exchange buffer, so that an exchange's
+    // loads are issued one whole stage of the other phase (about 200 VALU instructions) before
+    // their use; the next template's spectra load during this template's last stages. With one
+    // phase after the other, waves spent 33% of their cycles waiting on LDS and memory counters
+    // (1024 points, row peaks of 2^20 bins x 765 templates); now 16%. With the twiddles folded into
+    // the butterflies (DftTw) that search went from 2.20 to 1.92 ms, the 2^22-bin plane slab of 201
+    // templates from 2.52 to 2.34 ms (the clock drops to 1.75 GHz while the plane is written), the
+    // 2^15-bin search from 26.1 to 21.4 us.
+    auto fence = [] {
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_sched_barrier(0);
+    };
+    float2* const bufA = lds;
+    float2* const bufB = lds + lds_slots<S>();
+    float2 w2[E / 2], w3[E / 2];
+    load_twiddles<S, E, R2, R3>(w2, tw, tid);
+    load_twiddles<S, E, R1, R3 * R2>(w3, tw, tid);
+    // lane i: template of member m0 + i (at most 64 templates per block)
+    const int mine = min(m0 + tid, m1 - 1);
+    const int t_lane = TABLE ? ((gci32_ptr)j.members)[mine] : j.members[mine];
+    float2 hA[E], hB[E], a[E], b[E];
+    float P0[E];
+    load_h(hA, m0, 0);
+    for (int mm = m0; mm < m1; ++mm) {
+      const int next = min(mm + 1, m1 - 1);
+      load_h(hB, mm, 1);
+      fence();
+      // phase 0: product and first pass
+      product_pass<E, R3>(a, F, hA);
+      exchange_write<S, E, R3, 1>(a, bufA, tid);
+      fence();
+      exchange_read<S, E, R2, 1>(a, bufA, tid);
+      fence();
+      // phase 1: product and first pass
+      product_pass<E, R3>(b, F, hB);
+      exchange_write<S, E, R3, 1>(b, bufB, tid);
+      fence();
+      exchange_read<S, E, R2, 1>(b, bufB, tid);
+      fence();
+      // second passes
+      pass_compute<E, R2, R3, true>(a, w2);
+      exchange_write<S, E, R2, R3>(a, bufA, tid);
+      fence();
+      exchange_read<S, E, R1, R3>(a, bufA, tid);
+      fence();
+      pass_compute<E, R2, R3, true>(b, w2);
+      exchange_write<S, E, R2, R3>(b, bufB, tid);
+      fence();
+      exchange_read<S, E, R1, R3>(b, bufB, tid);
+      load_h(hA, next, 0);
+      fence();
+      // last passes
+      pass_compute<E, R1, R3 * R2, true>(a, w3);
+#pragma unroll
+      for (int e = 0; e < E; ++e) P0[e] = fmaf(a[e].x, a[e].x, a[e].y * a[e].y);
+      __builtin_amdgcn_sched_barrier(0);
+      pass_compute<E, R1, R3 * R2, true>(b, w3);
+      emit(mm, __builtin_amdgcn_readlane(t_lane, mm - m0), P0, b);
+    }
+  } else {
+    for (int mm = m0; mm < m1; ++mm) {
+      const int t = TABLE ? ((gci32_ptr)j.members)[mm] : j.members[mm];
+      float P0[E];
+#pragma unroll
+      for (int phase = 0; phase < 2; ++phase) {
+        float2 h[E];
+        load_h(h, mm, phase);
+        product_pass<E, RL>(v, F, h);
+        exchange_write<S, E, RL, 1>(v, lds, tid);
+        __syncthreads();
+        if constexpr (P4) {
+          stockham_pass<S, E, R3, R4, true, true, true, R4>(v, lds, tw, tid);
+          stockham_pass<S, E, R2, R4 * R3, true, true, true, R3>(v, lds, tw, tid);
+          stockham_pass<S, E, R1, R4 * R3 * R2, true, true, false, R2>(v, lds, tw, tid);
+        } else {
+          stockham_pass<S, E, R2, R3, true, true, true, R3>(v, lds, tw, tid);
+          stockham_pass<S, E, R1, R3 * R2, true, true, false, R2>(v, lds, tw, tid);
+        }
+        if (phase == 0) {
+#pragma unroll
+          for (int e = 0; e < E; ++e) P0[e] = fmaf(v[e].x, v[e].x, v[e].y * v[e].y);
+        } else {
+          emit(mm, t, P0, v);
         }
       }
     }
@@ -585,9 +776,9 @@ __device__ __forceinline__ void fft_tile(const FftJob& j, int64_t seg, int m0, i
 // One job, one workgroup per tile: blockIdx = tb * n_seg + seg. KEYS: write
 // peak keys (j.row_max) as well as (or instead of) the plane.
 template <int S, int E, int R1, int R2, int R3, int R4, bool KEYS>
-__global__ void __launch_bounds__(S / E) fft_correlate_kernel(FftJob j, const float2* __restrict__ tw) {
+__global__ void __launch_bounds__(S / E, (min_waves<S, E, R4>())) fft_correlate_kernel(FftJob j, const float2* __restrict__ tw) {
   static_assert(R1 * R2 * R3 * R4 == S, "radices must multiply to S");
-  __shared__ float2 lds[lds_slots<S>()];
+  __shared__ float2 lds[lds_total<S, E, R4>()];
   __shared__ uint64_t red[8];
   const int64_t blk = blockIdx.x;
   const int m0 = j.m_begin + (int)(blk / j.n_seg) * j.tpb;
@@ -602,7 +793,7 @@ template <int S, int E, int R1, int R2, int R3, int R4, bool KEYS>
 __global__ void __launch_bounds__(S / E) fft_persistent_kernel(const FftJob* __restrict__ jobs,
                                                                BatchHeader* __restrict__ hdr,
                                                                const float2* __restrict__ tw) {
-  __shared__ float2 lds[lds_slots<S>()];
+  __shared__ float2 lds[lds_total<S, E, R4>()];
   __shared__ uint64_t red[8];
   __shared__ int64_t s_tile;
   const int64_t total = hdr->total_tiles;
@@ -637,10 +828,10 @@ __global__ void __launch_bounds__(S / E) fft_persistent_kernel(const FftJob* __r
 // One launch over a job table, one workgroup per tile (grid = total tiles):
 // workgroup i takes tile i, the hardware dispatcher balancing the load.
 template <int S, int E, int R1, int R2, int R3, int R4, bool KEYS>
-__global__ void __launch_bounds__(S / E) fft_multi_kernel(const FftJob* __restrict__ jobs,
+__global__ void __launch_bounds__(S / E, (min_waves<S, E, R4>())) fft_multi_kernel(const FftJob* __restrict__ jobs,
                                                           const BatchHeader* __restrict__ hdr,
                                                           const float2* __restrict__ tw) {
-  __shared__ float2 lds[lds_slots<S>()];
+  __shared__ float2 lds[lds_total<S, E, R4>()];
   __shared__ uint64_t red[8];
   const int64_t tile = blockIdx.x;
   const int n_jobs = hdr->n_jobs;
@@ -665,8 +856,8 @@ struct FftArgJobs {
 };
 
 template <int S, int E, int R1, int R2, int R3, int R4, bool KEYS>
-__global__ void __launch_bounds__(S / E) fft_args_kernel(FftArgJobs m, const float2* __restrict__ tw) {
-  __shared__ float2 lds[lds_slots<S>()];
+__global__ void __launch_bounds__(S / E, (min_waves<S, E, R4>())) fft_args_kernel(FftArgJobs m, const float2* __restrict__ tw) {
+  __shared__ float2 lds[lds_total<S, E, R4>()];
   __shared__ uint64_t red[8];
   const int64_t tile = blockIdx.x;
   int k = 0;
@@ -682,9 +873,9 @@ __global__ void __launch_bounds__(S / E) fft_args_kernel(FftArgJobs m, const flo
 // the flagged rows, one template per tile, the grid striding over (flagged row,
 // segment) tiles; with no flagged row every workgroup exits at once.
 template <int S, int E, int R1, int R2, int R3, int R4, int CAND>
-__global__ void __launch_bounds__(S / E) fft_cand_kernel(FftJob j, const float2* __restrict__ tw, CandArgs ca) {
+__global__ void __launch_bounds__(S / E, (CAND == 1 ? min_waves<S, E, R4>() : 1)) fft_cand_kernel(FftJob j, const float2* __restrict__ tw, CandArgs ca) {
   constexpr int W = S / E / 64;
-  __shared__ float2 lds[lds_slots<S>()];
+  __shared__ float2 lds[lds_total<S, E, R4>()];
   __shared__ uint64_t red[8];
   __shared__ float xch[2 * W * E];
   __shared__ double2 wsum[W];
