@@ -19,38 +19,39 @@ bool seg_len_supported(int32_t s) { return s == 512 || s == 1024 || s == 2048 ||
 
 namespace {
 
-// 16-point Gauss-Legendre rule on [-1, 1] by Newton's method on P_16.
+// 16-point Gauss-Legendre rule on [-1, 1] by Newton's method on P_16, in extended
+// precision so that each node and weight is rounded once.
 void gauss_legendre16(double* x, double* w) {
   const int n = 16;
-  const double pi = 3.14159265358979323846;
+  const long double pi = 3.14159265358979323846L;
   for (int i = 0; i < n / 2; ++i) {
-    double z = std::cos(pi * (i + 0.75) / (n + 0.5));
-    double dp = 0.0;
+    long double z = std::cos(pi * (i + 0.75) / (n + 0.5));
+    long double dp = 0.0L;
     for (int it = 0; it < 100; ++it) {
-      double p0 = 1.0, p1 = z;  // P_0, P_1
+      long double p0 = 1.0L, p1 = z;  // P_0, P_1
       for (int k = 2; k <= n; ++k) {
-        double pk = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
+        long double pk = ((2.0L * k - 1.0L) * z * p1 - (k - 1.0L) * p0) / k;
         p0 = p1;
         p1 = pk;
       }
-      dp = n * (z * p1 - p0) / (z * z - 1.0);  // P_n'(z)
-      double dz = p1 / dp;
+      dp = n * (z * p1 - p0) / (z * z - 1.0L);  // P_n'(z)
+      long double dz = p1 / dp;
       z -= dz;
-      if (std::fabs(dz) < 1e-17) break;
+      if (std::fabs(dz) < 1e-19L) break;
     }
     // recompute the derivative at the converged root for the weight
-    double p0 = 1.0, p1 = z;
+    long double p0 = 1.0L, p1 = z;
     for (int k = 2; k <= n; ++k) {
-      double pk = ((2.0 * k - 1.0) * z * p1 - (k - 1.0) * p0) / k;
+      long double pk = ((2.0L * k - 1.0L) * z * p1 - (k - 1.0L) * p0) / k;
       p0 = p1;
       p1 = pk;
     }
-    dp = n * (z * p1 - p0) / (z * z - 1.0);
-    double wt = 2.0 / ((1.0 - z * z) * dp * dp);
-    x[i] = -z;
-    x[n - 1 - i] = z;
-    w[i] = wt;
-    w[n - 1 - i] = wt;
+    dp = n * (z * p1 - p0) / (z * z - 1.0L);
+    long double wt = 2.0L / ((1.0L - z * z) * dp * dp);
+    x[i] = (double)-z;
+    x[n - 1 - i] = (double)z;
+    w[i] = (double)wt;
+    w[n - 1 - i] = (double)wt;
   }
 }
 
