@@ -69,3 +69,13 @@ def test_prepared_spectrum_feeds_the_search():
     torch.cuda.synchronize()
     flat = int(torch.argmax(plane).item())
     assert divmod(flat, 2 * n) == (102, 16013)
+
+
+@pytest.mark.parametrize("log_n", [12, 14, 15, 17, 25])
+def test_pass_plans(log_n):
+    """The edges of the transform's pass plan: the largest one-workgroup length (2^11 points), one
+    pass before the last (6 and 7 bits; 5 above, in the noise series), two (2^16), the partial sums
+    folded (2^24)."""
+    rng = np.random.default_rng(log_n)
+    x = rng.standard_normal(1 << log_n).astype(np.float32)
+    _compare(_gpu_spectrum(x), prepare_spectrum(x))
