@@ -32,6 +32,14 @@ constexpr int kPeakTilesPerBlock = 32;                        // a block scans 3
 constexpr int kStage = 2048;                                  // LDS candidate staging slots
 constexpr int kMaxGridY = 65535;
 
+typedef float f4vec __attribute__((ext_vector_type(4)));
+// A stored plane is far larger than the caches and the statistics read it once: non-temporal loads
+// stream it at 7.1 TB/s on this device, plain ones at 6.4. (The peak finder reads neighbours out
+// of the cache again: its loads stay plain, non-temporal ones made it 8% slower.)
+__device__ __forceinline__ f4vec nt_load4(const float* p) {
+  return __builtin_nontemporal_load(reinterpret_cast<const f4vec*>(p));
+}
+
 struct Moments {
   double n, m, m2;  // count, mean, sum of squared deviations from the mean
 };
@@ -58,6 +66,10 @@ __device__ __forceinline__ Moments shfl_xor_moments(Moments v, int off) {
 }
 
 // grid (chunks, min(rows, 65535)); chunk c of a row covers [c * span, (c + 1) * span).
+// Whole tiles of aligned rows take a path of their own: the next tile's loads are in flight during
+// a tile's FP64 arithmetic, and the pairwise update takes its quotient of counts from a table
+// instead of a division per 16 values. Bound by the read: 128 rows of 2^22 points 394 -> 318 us
+// (5.4 -> 6.75 TB/s).
 // VEC: rows are 16-byte aligned (plane aligned, ld a multiple of 4), so a thread's
 // 16 values of a tile are four coalesced float4 loads; otherwise 16 scalar loads.
 template <bool VEC>
@@ -68,10 +80,47 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
   const int64_t lo = (int64_t)blockIdx.x * span;
   const int64_t hi = lo + span < n_r ? lo + span : n_r;
   __shared__ Moments red[kStatThreads / 64];
+  __shared__ double inv[kStatThreads];  // 1 / (i + 1): group i + 1 of 16 values joins i of them
+  inv[threadIdx.x] = 1.0 / (double)(threadIdx.x + 1);
+  __syncthreads();
   for (int32_t row = blockIdx.y; row < rows; row += gridDim.y) {
     const float* src = plane + (int64_t)row * ld;
     Moments acc{0.0, 0.0, 0.0};
-    for (int64_t base = lo; base < hi; base += kStatTile) {
+    int64_t base = lo;
+    if constexpr (VEC) {
+      // whole tiles, the next one's loads in flight during this one's arithmetic
+      const int32_t whole = (int32_t)((hi - lo) / kStatTile);
+      f4vec f[4];
+      auto load = [&](int64_t at) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f[q] = nt_load4(src + at + 4 * (q * kStatThreads + (int)threadIdx.x));
+      };
+      if (whole > 0) load(lo);
+      for (int32_t i = 0; i < whole; ++i) {
+        float v[kStatPerThread];
+#pragma unroll
+        for (int e = 0; e < kStatPerThread; ++e) v[e] = f[e / 4][e % 4];
+        base += kStatTile;
+        if (i + 1 < whole) load(base);
+        double sum = 0.0;
+#pragma unroll
+        for (int e = 0; e < kStatPerThread; ++e) sum += (double)v[e];
+        const double m = sum * (1.0 / kStatPerThread);
+        double m2 = 0.0;
+#pragma unroll
+        for (int e = 0; e < kStatPerThread; ++e) {
+          const double d = (double)v[e] - m;
+          m2 = fma(d, d, m2);
+        }
+        // the pairwise update of merge() for counts 16 i and 16
+        const double fb = i < kStatThreads ? inv[i] : 1.0 / (double)(i + 1);
+        const double d = m - acc.m;
+        acc.m2 = (acc.m2 + m2) + d * d * acc.n * fb;
+        acc.m = i == 0 ? m : acc.m + d * fb;
+        acc.n += (double)kStatPerThread;
+      }
+    }
+    for (; base < hi; base += kStatTile) {
       float v[kStatPerThread];
       bool ok[kStatPerThread];
 #pragma unroll
@@ -79,7 +128,7 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
         // element e = 4 (q * 256 + tid) + c of the tile
         const int64_t p0 = base + 4 * ((int64_t)q * kStatThreads + threadIdx.x);
         if (VEC && p0 + 3 < hi) {
-          const float4 f = *reinterpret_cast<const float4*>(src + p0);
+          const f4vec f = nt_load4(src + p0);
           v[4 * q + 0] = f.x;
           v[4 * q + 1] = f.y;
           v[4 * q + 2] = f.z;

@@ -185,3 +185,52 @@ def test_full_size_slab_2e22_bins():
         _check_stats(st[i: i + 1], row)
         sub = got[got["t"] == members[i]]
         _check_candidates(sub, row, 5.0, row_template=[members[i]])
+
+
+@pytest.mark.parametrize("n_r,ld", [(255, 256), (2048, 2048), (32769, 32772), (70001, 70001)])
+def test_densest_peaks(n_r, ld):
+    """Every other point a peak, the most a row can hold: the staging slots fill and are flushed
+    several times per row."""
+    import torch
+    dev = device()
+    rng = np.random.default_rng(n_r)
+    plane = np.full((3, ld), np.nan, dtype=np.float32)
+    plane[:, :n_r] = rng.uniform(0.0, 0.5, (3, n_r)).astype(np.float32)
+    plane[0, :n_r:2] += 1.0
+    plane[1, 1:n_r:2] += 1.0
+    stats = np.tile(np.array([0.6, 0.1]), (3, 1))
+    cap = 3 * n_r
+    out = torch.zeros((cap, 4), dtype=torch.int32, device=dev)
+    count = torch.zeros(1, dtype=torch.int64, device=dev)
+    d = torch.from_numpy(plane).to(dev)
+    J.find_candidates(d[:, :n_r], torch.from_numpy(stats).to(dev), 2.0, out, count)
+    torch.cuda.synchronize()
+    got = J.candidates_numpy(out, count)
+    want = []
+    for t in range(3):
+        x = plane[t, :n_r].astype(np.float64)
+        left = np.concatenate([[-np.inf], x[:-1]])
+        right = np.concatenate([x[1:], [-np.inf]])
+        want += [(t, p) for p in np.flatnonzero((x > left) & (x >= right) & (x > 0.6 + 2.0 * 0.1))]
+    assert len(want) > n_r // 2
+    assert sorted((int(r["t"]), int(r["p"])) for r in got) == want
+    assert all(r["power"] == plane[r["t"], r["p"]] for r in got)
+
+
+def test_statistics_of_many_long_rows():
+    """One chunk per row and more than 256 whole tiles in it, then a remainder of two float4."""
+    import torch
+    dev = device()
+    rows, n_r = 4096, 4096 * 257 + 8
+    g = torch.Generator(device=dev)
+    g.manual_seed(5)
+    plane = torch.empty((rows, n_r), dtype=torch.float32, device=dev).exponential_(generator=g)
+    stats = torch.empty((rows, 2), dtype=torch.float64, device=dev)
+    J.plane_stats(plane, stats)
+    torch.cuda.synchronize()
+    for r in (0, 2047, 4095):
+        x = plane[r].double()
+        mean = x.mean()
+        sigma = (x - mean).square().mean().sqrt()
+        assert abs(stats[r, 0] - mean) <= 1e-12 * mean
+        assert abs(stats[r, 1] - sigma) <= 1e-12 * sigma
