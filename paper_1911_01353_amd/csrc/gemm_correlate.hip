@@ -181,11 +181,10 @@ __device__ __forceinline__ void gemm_tile(const GemmArgs& a, int64_t windows_per
         for (int pp = 0; pp < P; ++pp)
           afr[r][q][pp] = (ks0 + q < KS) ? *frag_ptr(rb0 + r, ks0 + q, pp) : make_uint4(0, 0, 0, 0);
   };
-  // Split-BF16 resident fragments are kept in the order the main loop visits
-  // k-steps: slot (part * 2 + parity) * NI + i holds k-step part * ksr + parity + 2 i.
-  // (FP16 keeps k-step order: its 32 resident slots leave no room for the
-  // fragment ring below.)
-  constexpr bool REUSE = RESIDENT && SPLIT;
+  // Resident fragments of a compile-time tap count (and all split-BF16 ones) are kept in
+  // the order the main loop visits k-steps: slot (part * 2 + parity) * NI + i holds k-step
+  // part * ksr + parity + 2 i.
+  constexpr bool REUSE = RESIDENT && (SPLIT || KT > 0);
   constexpr int NI = KC / 4 > 0 ? KC / 4 : 1;
   if constexpr (!REUSE && RESIDENT) load_frags(0);
   if constexpr (REUSE && NW == 1) {
@@ -466,8 +465,21 @@ gemm_correlate_mw_kernel(GemmArgs a, int64_t windows_per_wg, int64_t n_colchunks
   gemm_tile<1, CT, KC, MAXLD, true, true, KEYS, KT, NW>(a, windows_per_wg, n_colchunks, blockIdx.x, lds32);
 }
 
+// FP16: one kernel body per tap count, so that the fragment ring applies (one LDS fragment per
+// k-step instead of one per column tile) and no tap count is checked in the loops; 128 outputs per
+// window. One body for all tap counts with 64 outputs per window read two fragments per two MFMAs,
+// which is all the LDS delivers; 303 templates of 32 to 144 taps over 2^20 bins: 968 -> 707 us
+// (3.6 TB/s written; MFMA 36% busy, bound by the stores and their power). Tap counts of these
+// kernels, their k-step slots (two runs of
+// ceil(K / 32) per part) and the loads of a 128-output window per lane.
+#define JERK_FP16_NARROW_TAPS(X) X(16) X(32) X(48) X(64) X(80) X(96) X(112) X(128)
+#define JERK_FP16_WIDE_TAPS(X) X(144) X(160) X(176) X(192) X(208) X(224) X(240) X(256)
+constexpr int fp16_ct(int K) { return K <= 192 ? 4 : 2; }
+constexpr int fp16_slots(int K) { return 4 * ((K + 31) / 32); }
+constexpr int fp16_loads(int K) { return (32 * fp16_ct(K) + K + 8 + 63) / 64; }
+
 // Several narrow width groups in one launch (split-BF16 with at most 64 taps, or FP16 with
-// at most 256): workgroup i belongs to the job whose block range holds it and runs that
+// at most 128): workgroup i belongs to the job whose block range holds it and runs that
 // job's kernel body (one per tap count), so a small search is one launch instead of one per
 // group. The job table travels in the kernel arguments.
 constexpr int kGemmMultiJobs = 8;
@@ -495,7 +507,12 @@ __global__ void __launch_bounds__(64, 2) gemm_multi_kernel(GemmMulti m) {
       default: gemm_tile<1, 4, 8, 4, true, true, KEYS, 64>(a, m.windows_per_wg[j], m.n_colchunks[j], local, lds32); break;
     }
   } else {
-    gemm_tile<1, 2, 32, 6, false, true, KEYS, 0>(a, m.windows_per_wg[j], m.n_colchunks[j], local, lds32);
+    switch (a.taps) {
+#define X(K) \
+  case K: gemm_tile<1, 4, fp16_slots(K), fp16_loads(K), false, true, KEYS, K>(a, m.windows_per_wg[j], m.n_colchunks[j], local, lds32); break;
+      JERK_FP16_NARROW_TAPS(X)
+#undef X
+    }
   }
 }
 
@@ -671,8 +688,21 @@ void launch_split_resident(const GemmArgs& a, hipStream_t stream) {
   }
 }
 
+// FP16 groups of up to 256 taps: one kernel per tap count, 128 outputs per window (64 above 192
+// taps, whose fragments would leave no registers for the rest).
+template <bool KEYS>
+void launch_fp16_resident(const GemmArgs& a, hipStream_t stream) {
+  switch (a.taps) {
+#define X(K) case K: launch_cfg<1, fp16_ct(K), fp16_slots(K), fp16_loads(K), false, true, KEYS, K>(a, stream); break;
+    JERK_FP16_NARROW_TAPS(X)
+    JERK_FP16_WIDE_TAPS(X)
+#undef X
+    default: throw Error(JERK_EINTERNAL, "FP16 tap count without a kernel");
+  }
+}
+
 bool gemm_multi_eligible(const GemmArgs& a) {
-  return a.path == JERK_PATH_GEMM_FP16 ? a.taps <= 256 : a.taps <= 64;
+  return a.path == JERK_PATH_GEMM_FP16 ? a.taps <= 128 : a.taps <= 64;
 }
 
 // One launch for jobs[0..n) (2 <= n <= 8), all eligible, all split-BF16 or all FP16, all with
@@ -690,7 +720,7 @@ void gemm_correlate_multi_launch(const GemmArgs* jobs, int n, hipStream_t stream
     require((a.path != JERK_PATH_GEMM_FP16) == split && (a.row_max != nullptr) == keys && gemm_multi_eligible(a),
             JERK_EINTERNAL, "GEMM jobs of one launch must share path and key mode");
     require(a.m_begin % 8 == 0 && a.taps % 16 == 0 && a.taps >= 16, JERK_EINTERNAL, "bad GEMM job");
-    const int ct = split ? 4 : 2;
+    const int ct = 4;
     const GemmGrid gg = gemm_grid(a, 1, ct);
     m.job[i] = a;
     m.windows_per_wg[i] = gg.windows_per_wg;
@@ -727,14 +757,14 @@ void gemm_correlate_launch(const GemmArgs& a, hipStream_t stream) {
       if (a.taps <= 128) launch_split_resident<true>(a, stream);
       else launch_split_streamed<true>(a, stream);
     } else {
-      if (a.taps <= 256) launch_cfg<1, 2, 32, 6, false, true, true>(a, stream);
+      if (a.taps <= 256) launch_fp16_resident<true>(a, stream);
       else launch_cfg<1, 2, 16, 10, false, false, true>(a, stream);
     }
   } else if (split) {
     if (a.taps <= 128) launch_split_resident<false>(a, stream);
     else launch_split_streamed<false>(a, stream);
   } else {
-    if (a.taps <= 256) launch_cfg<1, 2, 32, 6, false, true, false>(a, stream);
+    if (a.taps <= 256) launch_fp16_resident<false>(a, stream);
     else launch_cfg<1, 2, 16, 10, false, false, false>(a, stream);
   }
   JERK_HIP_CHECK(hipGetLastError());

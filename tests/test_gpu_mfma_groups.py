@@ -64,3 +64,34 @@ def test_peak_keys_equal_plane_row_maxima():
     assert np.array_equal(pk["power"].view(np.uint32), plane[np.arange(plane.shape[0]), idx].view(np.uint32))
     assert np.array_equal(pk["p"].astype(np.int64), idx)
     plan.close()
+
+
+@pytest.mark.parametrize("path,tol", [("fp16", 1e-2), ("split_bf16", 1e-4)])
+@pytest.mark.parametrize("taps", list(range(16, 273, 16)))
+def test_every_tap_count(taps, path, tol):
+    """One kernel per tap count (the first tap count above them included): plane rows against the FP64
+    correlation with the bank's taps, over several windows and a ragged end; row peaks against the
+    plane's."""
+    import torch
+    from gpu_helpers import bank_taps
+    dev = device()
+    n = 701
+    plan = J.Plan(n, 15.0, 0.0, 2.0, 20.0, path=path, margin=taps // 2 - 8, tap_quantum=taps)
+    assert [g["taps"] for g in plan.groups()] == [taps]
+    bank = build_bank(plan)
+    rng = np.random.default_rng(taps)
+    spec = ((rng.standard_normal(n) + 1j * rng.standard_normal(n)) / np.sqrt(2)).astype(np.complex64)
+    plane = gpu_plane(plan, bank, spec)
+    x = np.concatenate([np.zeros(taps // 2 - 1), spec.astype(np.complex128), np.zeros(taps // 2)])
+    coef = bank_taps(plan, bank, 0)
+    for k, t in enumerate(plan.members()):
+        want = np.empty(2 * n)
+        for phase in (0, 1):
+            want[phase::2] = np.abs(np.correlate(x, np.conj(coef[k, phase]))) ** 2
+        err = np.abs(plane[t] - want) / np.maximum(want, want.mean())
+        assert err.max() <= tol, (t, err.max())
+    got = J.peaks_numpy(plan.search_peaks(bank, torch.from_numpy(spec).to(dev)), plane.shape[0])
+    torch.cuda.synchronize()
+    assert np.array_equal(got["p"].astype(np.int64), plane.argmax(axis=1))
+    assert np.array_equal(got["power"], plane.max(axis=1))
+    plan.close()
