@@ -130,16 +130,20 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
       j.t_begin = t_begin;
       j.taps = g.taps;
       j.tpb = g.tpb;
+      j.tpb_auto = g.tpb_auto;
       j.plane = it.plane;
       j.ld = it.ld;
       j.row_max = it.peaks;
       j.rmax_ld = it.keys_ld;
-      j.tile_begin = total;
-      total += fft_job_tiles(j, seg);
       jobs.push_back(j);
     }
   }
   if (jobs.empty()) return;
+  fft_balance(jobs.data(), (int)jobs.size(), seg, ept);
+  for (FftJob& j : jobs) {
+    j.tile_begin = total;
+    total += fft_job_tiles(j, seg);
+  }
 
   if (!p.batch) p.batch = new BatchCtx();
   BatchCtx& c = *p.batch;

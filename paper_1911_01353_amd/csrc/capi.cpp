@@ -113,6 +113,7 @@ void search_enqueue(const Plan& p, const void* d_bank, const void* d_spec, int64
       j.ld = ld;
       j.taps = g.taps;
       j.tpb = g.tpb;
+      j.tpb_auto = g.tpb_auto;
       j.row_max = row_max;
       j.rmax_ld = 0;
       const int64_t U = g.seg_len - g.taps + 1;
@@ -172,6 +173,7 @@ void search_members_enqueue(const Plan& p, const void* d_bank, const void* d_spe
     j.ld = ld;
     j.taps = g.taps;
     j.tpb = g.tpb;
+    j.tpb_auto = g.tpb_auto;
     fft_correlate_launch(j, g.seg_len, g.ept, reinterpret_cast<const float2*>(bank + p.off_tw[tw_slot(g.seg_len)]),
                          stream);
   } else {
@@ -340,6 +342,7 @@ int32_t jerk_plan_set_group(jerk_plan* plan, int32_t g, int32_t seg_len, int32_t
             "no FFT kernel variant with this segment length and elements per thread");
     G.seg_len = seg_len;
     G.tpb = templates_per_block;
+    G.tpb_auto = false;
     G.path = path;
     G.ept = fft_ept;
     jerk::plan_layout(p);

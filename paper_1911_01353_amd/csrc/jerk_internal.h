@@ -40,6 +40,7 @@ struct Group {
   int32_t seg_len = 0;     // S_g
   int32_t ept = 16;        // FFT kernel variant: complex elements per thread (8 or 16)
   int32_t tpb = 8;         // templates per workgroup (FFT path)
+  bool tpb_auto = false;   // by default rule: launches may share the templates out otherwise (fft_balance)
   int32_t path = JERK_PATH_FFT_FP32;
   std::vector<int32_t> members;  // template indices, ascending
   int32_t first_member = 0;      // offset in the concatenated member table
@@ -101,6 +102,7 @@ struct FftJob {
   int32_t row_by_member;      // ... or, when set, mm - row_base for group member mm
   int32_t row_base;
   int32_t taps, tpb;
+  int32_t tpb_auto;           // tpb may be changed by fft_balance
   float* plane;               // plane rows (row stride ld floats), or null
   int64_t ld;
   uint64_t* row_max;          // peak keys [row][segment] (row stride rmax_ld), or null;
@@ -181,6 +183,9 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
                        int64_t capacity, unsigned long long* d_count, int64_t staged, void* d_ws, size_t ws_bytes,
                        hipStream_t stream);
 
+// Shares the templates of the jobs of one flat launch (those with tpb_auto) out over workgroups
+// again, by the size of the launch. Only speed depends on it.
+void fft_balance(FftJob* jobs, int n, int32_t seg_len, int32_t ept);
 // Sets j.n_seg and returns the job's tile count (segments x template blocks).
 int64_t fft_job_tiles(FftJob& j, int32_t seg_len);
 // twiddles: exp(-2 pi i k / seg_len), k < seg_len (complex64, device).

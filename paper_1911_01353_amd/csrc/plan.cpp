@@ -184,6 +184,7 @@ void plan_build(Plan& p, const jerk_plan_desc& d) {
     require(g.seg_len >= 2 * g.taps, JERK_EINVAL, "seg_len must be at least twice the widest group's taps");
     g.tpb = d.templates_per_block ? d.templates_per_block
                                   : default_tpb(d.nbins, g.seg_len, g.taps, (int64_t)g.members.size());
+    g.tpb_auto = d.templates_per_block == 0;
     g.ept = default_ept(g.seg_len);
     if (d.path == JERK_PATH_AUTO) {
       g.path = g.taps <= kAutoGemmMaxTaps ? JERK_PATH_GEMM_SPLIT_BF16 : JERK_PATH_FFT_FP32;

@@ -166,7 +166,6 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
   uint32_t* n_flagged = reinterpret_cast<uint32_t*>(ws + L.n_flagged);
   int32_t* ovf = reinterpret_cast<int32_t*>(ws + L.ovf);
   uint32_t* tile_hits = reinterpret_cast<uint32_t*>(ws + L.tile_hits);
-  CandHit* hits = reinterpret_cast<CandHit*>(ws + L.hits);
   CandPoolHit* pool = reinterpret_cast<CandPoolHit*>(ws + L.pool);
   unsigned long long* pool_count = reinterpret_cast<unsigned long long*>(ws + L.n_flagged + 64);
   const char* bank = static_cast<const char*>(d_bank);
@@ -203,14 +202,37 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
     j.row_by_member = 1;
     j.row_base = lo;
     j.taps = g.taps;
-    j.tpb = g.tpb;
     const int32_t U = g.seg_len - g.taps + 1;
     const int64_t n_seg = group_segments(g, nbins);
     const int32_t rows = hi - lo;
     const int32_t* row_t = j.members + lo;  // template of row r
     const float2* tw = reinterpret_cast<const float2*>(bank + p.off_tw[tw_slot(g.seg_len)]);
-    const int32_t cap = group_cap(g, pre, staged);
-    const int64_t tiles = group_tiles(g, rows, nbins);
+    int32_t cap = group_cap(g, pre, staged);
+    int64_t tiles = group_tiles(g, rows, nbins);
+    size_t hit_counts = L.hits - L.tile_hits;  // bytes of the tiles' hit counts, the slots behind them
+    j.tpb = g.tpb;
+    if (g.tpb_auto && staged <= 0) {
+      // Other blocks where the launch gains by them (fft_balance) and the space the layout has for
+      // g.tpb still gives each tile twice its expected hits and four.
+      FftJob b = j;
+      b.tpb_auto = 1;
+      fft_balance(&b, 1, g.seg_len, g.ept);
+      Group bg;
+      bg.taps = g.taps;
+      bg.seg_len = g.seg_len;
+      bg.tpb = b.tpb;
+      const int64_t b_tiles = group_tiles(bg, rows, nbins);
+      const size_t counts = align_up((size_t)b_tiles * sizeof(uint32_t)), space = L.pool - L.tile_hits;
+      const int64_t full = group_cap(bg, pre, 0);
+      const int64_t slots = space > counts ? (int64_t)((space - counts) / sizeof(CandHit)) / b_tiles : 0;
+      if (b_tiles < (int64_t(1) << 31) && slots >= full - 12) {
+        j.tpb = b.tpb;
+        tiles = b_tiles;
+        cap = (int32_t)std::min(full, slots);
+        hit_counts = counts;
+      }
+    }
+    CandHit* const hits = reinterpret_cast<CandHit*>(ws + L.tile_hits + hit_counts);
     CandArgs ca{};
     ca.pre = pre;
     ca.part = part;
@@ -232,7 +254,7 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
     fft_cand_launch(j, g.seg_len, g.ept, tw, ca, 1, stream);
     cand_finish(part, rows, n_seg, U, nbins, ovf, k_sigma, pre, row_t, t_begin, d_stats, rs, flagged, n_flagged,
                 stream);
-    cand_filter(hits, tile_hits, (int32_t)tiles, cap, (int32_t)n_seg, g.tpb, U, pool, pool_count, L.pool_cap, rs,
+    cand_filter(hits, tile_hits, (int32_t)tiles, cap, (int32_t)n_seg, j.tpb, U, pool, pool_count, L.pool_cap, rs,
                 row_t, d_out, capacity, d_count, stream);
     cand_edges(edge, rows, n_seg, U, nbins, rs, row_t, d_out, capacity, d_count, stream);
     fft_cand_launch(j, g.seg_len, g.ept, tw, ca, 2, stream);

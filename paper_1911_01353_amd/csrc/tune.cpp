@@ -260,6 +260,7 @@ void autotune(Plan& p, const void* d_spec, int64_t nbins, void* d_scratch, size_
       p.groups[gi].path = JERK_PATH_FFT_FP32;
       p.groups[gi].seg_len = bc.seg;
       p.groups[gi].tpb = bc.tpb;
+      p.groups[gi].tpb_auto = false;
       p.groups[gi].ept = bc.ept;
     }
   } else {
@@ -272,6 +273,7 @@ void autotune(Plan& p, const void* d_spec, int64_t nbins, void* d_scratch, size_
       if (best->first.path == JERK_PATH_FFT_FP32) {
         g.seg_len = best->first.seg;
         g.tpb = best->first.tpb;
+        g.tpb_auto = false;
         g.ept = best->first.ept;
       }
     }
