@@ -928,12 +928,12 @@ void fft_balance(FftJob* jobs, int n, int32_t seg_len, int32_t ept) {
   constexpr double kForward = 1.5;
   bool any = false;
   for (int i = 0; i < n; ++i) any = any || (jobs[i].tpb_auto && jobs[i].m_end > jobs[i].m_begin);
-  if (!any) return;
+  // measured on the default variant only: the others are asked for by segment length
+  if (!any || seg_len != 1024 || ept != 16) return;
   int dev = 0, cus = 0;
   JERK_HIP_CHECK(hipGetDevice(&dev));
   JERK_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  const int waves = seg_len / ept / 64;                                            // of a workgroup
-  const double places = (double)std::max(1, cus) * 4 * (ept == 16 ? 2 : 4) / waves;  // 2 (4) waves a SIMD fit
+  const double places = (double)std::max(1, cus) * 4 * 2;  // one-wave workgroups, two to a SIMD
   auto shared_out = [](const FftJob& j, int32_t tpb) {
     const int32_t m = j.m_end - j.m_begin, blocks = (m + tpb - 1) / tpb;
     return (m + blocks - 1) / blocks;

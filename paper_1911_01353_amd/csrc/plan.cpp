@@ -75,7 +75,9 @@ int32_t default_ept(int32_t seg_len) { return seg_len == 512 ? 8 : 16; }
 // let each segment's forward transform and spectrum reads serve more templates
 // (64 against 16 on the 2^22-bin search: 3.5% faster writing the plane, 7.5%
 // returning peaks); small searches need the smaller blocks to fill the device
-// (2^15 bins: 24.6 us at 4 per block against 63 us at 16).
+// (2^15 bins: 21.6 us at 4 per block; with the unpipelined kernel 24.6, and 63 at
+// 16). Launches of more than one round share their templates out anew
+// (fft_balance): this rule sees one whole group at the plan's length.
 int32_t default_tpb(int64_t nbins, int32_t seg_len, int32_t taps, int64_t members) {
   const int64_t n_seg = (nbins + (seg_len - taps + 1) - 1) / (seg_len - taps + 1);
   for (int32_t tpb : {64, 32, 16, 8})

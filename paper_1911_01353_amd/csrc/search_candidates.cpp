@@ -29,7 +29,9 @@
 // than tpb U, the most peaks a tile can hold (peaks are never adjacent). Tiles
 // with more hits (a strong signal leaks high powers into the r range around it
 // in every template) spill into a shared pool of half the slots (plus 2^16 with
-// the default slot count); only a hit that finds the pool full flags its row.
+// the default slot count); only a hit that finds the pool full flags its row. A
+// launch that takes other blocks than the plan's (fft_balance) lays its counts and
+// slots out in the same space.
 #include <algorithm>
 #include <cmath>
 
