@@ -479,9 +479,12 @@ constexpr int fp16_slots(int K) { return 4 * ((K + 31) / 32); }
 constexpr int fp16_loads(int K) { return (32 * fp16_ct(K) + K + 8 + 63) / 64; }
 
 // Several narrow width groups in one launch (split-BF16 with at most 64 taps, or FP16 with
-// at most 128): workgroup i belongs to the job whose block range holds it and runs that
+// at most 256): workgroup i belongs to the job whose block range holds it and runs that
 // job's kernel body (one per tap count), so a small search is one launch instead of one per
-// group. The job table travels in the kernel arguments.
+// group. The job table travels in the kernel arguments. The FP16 bodies up to 256 taps all fit
+// the two waves per SIMD that the narrow ones have; with the groups of 144 to 256 taps launched
+// each by itself, 201 templates of 32 to 240 taps took 40 us instead of 14 over 2^12 bins and
+// 52 instead of 32 over 2^15 (one body for all, in one launch: 16 and 43).
 constexpr int kGemmMultiJobs = 8;
 struct GemmMulti {
   GemmArgs job[kGemmMultiJobs];
@@ -509,8 +512,9 @@ __global__ void __launch_bounds__(64, 2) gemm_multi_kernel(GemmMulti m) {
   } else {
     switch (a.taps) {
 #define X(K) \
-  case K: gemm_tile<1, 4, fp16_slots(K), fp16_loads(K), false, true, KEYS, K>(a, m.windows_per_wg[j], m.n_colchunks[j], local, lds32); break;
+  case K: gemm_tile<1, fp16_ct(K), fp16_slots(K), fp16_loads(K), false, true, KEYS, K>(a, m.windows_per_wg[j], m.n_colchunks[j], local, lds32); break;
       JERK_FP16_NARROW_TAPS(X)
+      JERK_FP16_WIDE_TAPS(X)
 #undef X
     }
   }
@@ -702,7 +706,7 @@ void launch_fp16_resident(const GemmArgs& a, hipStream_t stream) {
 }
 
 bool gemm_multi_eligible(const GemmArgs& a) {
-  return a.path == JERK_PATH_GEMM_FP16 ? a.taps <= 128 : a.taps <= 64;
+  return a.path == JERK_PATH_GEMM_FP16 ? a.taps <= 256 : a.taps <= 64;
 }
 
 // One launch for jobs[0..n) (2 <= n <= 8), all eligible, all split-BF16 or all FP16, all with
@@ -720,7 +724,7 @@ void gemm_correlate_multi_launch(const GemmArgs* jobs, int n, hipStream_t stream
     require((a.path != JERK_PATH_GEMM_FP16) == split && (a.row_max != nullptr) == keys && gemm_multi_eligible(a),
             JERK_EINTERNAL, "GEMM jobs of one launch must share path and key mode");
     require(a.m_begin % 8 == 0 && a.taps % 16 == 0 && a.taps >= 16, JERK_EINTERNAL, "bad GEMM job");
-    const int ct = 4;
+    const int ct = split ? 4 : fp16_ct(a.taps);
     const GemmGrid gg = gemm_grid(a, 1, ct);
     m.job[i] = a;
     m.windows_per_wg[i] = gg.windows_per_wg;

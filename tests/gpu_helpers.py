@@ -44,3 +44,20 @@ def bank_taps(plan, bank, g):
     nbytes = info["n_members"] * 2 * info["taps"] * 16
     raw = bank[info["taps_offset"]: info["taps_offset"] + nbytes].cpu().numpy()
     return raw.view(np.complex128).reshape(info["n_members"], 2, info["taps"])
+
+
+def captured_kernels(enqueue):
+    """Number of nodes of the graph that capturing ``enqueue()`` on torch's current stream gives."""
+    import ctypes
+
+    import torch
+    g = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(g):
+        enqueue()
+    with open("/proc/self/maps") as f:
+        lib = next(line.split()[-1] for line in f if "libamdhip64" in line)
+    n = ctypes.c_size_t(0)
+    get = ctypes.CDLL(lib).hipGraphGetNodes
+    get.argtypes = [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_size_t)]
+    assert get(g.raw_cuda_graph(), None, ctypes.byref(n)) == 0
+    return n.value

@@ -95,3 +95,42 @@ def test_every_tap_count(taps, path, tol):
     assert np.array_equal(got["p"].astype(np.int64), plane.argmax(axis=1))
     assert np.array_equal(got["power"], plane.max(axis=1))
     plan.close()
+
+
+@pytest.mark.parametrize("n", [701, 5000])
+def test_wide_fp16_groups_share_launches(n):
+    """FP16 groups of 32 to 240 taps (one launch of eight groups, one of six): the kernels a search
+    queues, its plane against each group's own kernel (the same bits) and the FP64 correlation with
+    the bank's taps, its row peaks against the plane's."""
+    import torch
+    from gpu_helpers import bank_taps, captured_kernels
+    dev = device()
+    plan = J.Plan(n, 200.0, 0.0, 2.0, 20.0, path="fp16")
+    assert [g["taps"] for g in plan.groups()] == list(range(32, 241, 16))
+    T = plan.info()["n_templates"]
+    bank = build_bank(plan)
+    spec_np = _spec(n, 63)
+    spec = torch.from_numpy(spec_np).to(dev)
+    plane = gpu_plane(plan, bank, spec_np)
+    out = torch.full((T, 2 * n), float("nan"), dtype=torch.float32, device=dev)
+    assert captured_kernels(lambda: plan.search(bank, spec, out)) == 2
+    for gi in range(len(plan.groups())):
+        plan.search_group(bank, spec, out, gi)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().view(np.uint32), plane.view(np.uint32))
+    members = plan.members()
+    for gi, g in enumerate(plan.groups()):
+        coef = bank_taps(plan, bank, gi)
+        x = np.concatenate([np.zeros(g["taps"] // 2 - 1), spec_np.astype(np.complex128), np.zeros(g["taps"] // 2)])
+        for k in range(g["n_members"]):
+            t = members[g["first_member"] + k]
+            want = np.empty(2 * n)
+            for phase in (0, 1):
+                want[phase::2] = np.abs(np.correlate(x, np.conj(coef[k, phase]))) ** 2
+            err = np.abs(plane[t] - want) / np.maximum(want, want.mean())
+            assert err.max() <= 1e-2, (t, err.max())
+    got = J.peaks_numpy(plan.search_peaks(bank, spec), T)
+    torch.cuda.synchronize()
+    assert np.array_equal(got["p"].astype(np.int64), plane.argmax(axis=1))
+    assert np.array_equal(got["power"], plane.max(axis=1))
+    plan.close()
