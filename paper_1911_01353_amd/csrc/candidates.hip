@@ -66,13 +66,15 @@ __device__ __forceinline__ Moments shfl_xor_moments(Moments v, int off) {
 }
 
 // grid (chunks, min(rows, 65535)); chunk c of a row covers [c * span, (c + 1) * span).
-// Whole tiles of aligned rows take a path of their own: the next tile's loads are in flight during
-// a tile's FP64 arithmetic, and the pairwise update takes its quotient of counts from a table
-// instead of a division per 16 values. Bound by the read: 128 rows of 2^22 points 394 -> 318 us
-// (5.4 -> 6.75 TB/s).
 // VEC: rows are 16-byte aligned (plane aligned, ld a multiple of 4), so a thread's
 // 16 values of a tile are four coalesced float4 loads; otherwise 16 scalar loads.
-template <bool VEC>
+// STREAM (VEC, chunks of two tiles or more): whole tiles take a path of their own. The next
+// tile's loads are in flight during a tile's FP64 arithmetic, and the pairwise update takes its
+// quotient of counts from a table instead of a division per 16 values. Bound by the read: 128 rows
+// of 2^22 points 394 -> 318 us (5.4 -> 6.75 TB/s). Chunks of one tile or less have no next one, and
+// many short rows are bound by latency, where the wider kernel's fewer waves cost more: 20000 rows
+// of 100 points take 53 us, in it 62.
+template <bool VEC, bool STREAM>
 __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* __restrict__ plane, int64_t ld,
                                                                    int32_t rows, int64_t n_r, int64_t span,
                                                                    Moments* __restrict__ part) {
@@ -80,14 +82,16 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
   const int64_t lo = (int64_t)blockIdx.x * span;
   const int64_t hi = lo + span < n_r ? lo + span : n_r;
   __shared__ Moments red[kStatThreads / 64];
-  __shared__ double inv[kStatThreads];  // 1 / (i + 1): group i + 1 of 16 values joins i of them
-  inv[threadIdx.x] = 1.0 / (double)(threadIdx.x + 1);
-  __syncthreads();
+  __shared__ double inv[STREAM ? kStatThreads : 1];  // 1 / (i + 1): group i + 1 of 16 values joins i of them
+  if constexpr (STREAM) {
+    inv[threadIdx.x] = 1.0 / (double)(threadIdx.x + 1);
+    __syncthreads();
+  }
   for (int32_t row = blockIdx.y; row < rows; row += gridDim.y) {
     const float* src = plane + (int64_t)row * ld;
     Moments acc{0.0, 0.0, 0.0};
     int64_t base = lo;
-    if constexpr (VEC) {
+    if constexpr (STREAM) {
       // whole tiles, the next one's loads in flight during this one's arithmetic
       const int32_t whole = (int32_t)((hi - lo) / kStatTile);
       f4vec f[4];
@@ -128,7 +132,7 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
         // element e = 4 (q * 256 + tid) + c of the tile
         const int64_t p0 = base + 4 * ((int64_t)q * kStatThreads + threadIdx.x);
         if (VEC && p0 + 3 < hi) {
-          const f4vec f = nt_load4(src + p0);
+          const f4vec f = STREAM ? nt_load4(src + p0) : *reinterpret_cast<const f4vec*>(src + p0);
           v[4 * q + 0] = f.x;
           v[4 * q + 1] = f.y;
           v[4 * q + 2] = f.z;
@@ -595,12 +599,15 @@ void plane_stats(const float* plane, int64_t ld, int32_t rows, int64_t n_r, doub
   const int64_t span = (tiles + chunks - 1) / chunks * kStatTile;
   const dim3 grid((unsigned)chunks, (unsigned)(rows < kMaxGridY ? rows : kMaxGridY));
   const bool vec = (reinterpret_cast<uintptr_t>(plane) & 15u) == 0 && ld % 4 == 0;
-  if (vec)
-    hipLaunchKernelGGL(row_moments_kernel<true>, grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r, span,
-                       static_cast<Moments*>(ws));
+  if (vec && span >= 2 * kStatTile)
+    hipLaunchKernelGGL((row_moments_kernel<true, true>), grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r,
+                       span, static_cast<Moments*>(ws));
+  else if (vec)
+    hipLaunchKernelGGL((row_moments_kernel<true, false>), grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r,
+                       span, static_cast<Moments*>(ws));
   else
-    hipLaunchKernelGGL(row_moments_kernel<false>, grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r, span,
-                       static_cast<Moments*>(ws));
+    hipLaunchKernelGGL((row_moments_kernel<false, false>), grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r,
+                       span, static_cast<Moments*>(ws));
   JERK_HIP_CHECK(hipGetLastError());
   hipLaunchKernelGGL(row_stats_finish_kernel, dim3((unsigned)((rows + 255) / 256)), dim3(256), 0, stream,
                      static_cast<const Moments*>(ws), rows, chunks, stats);

@@ -234,3 +234,23 @@ def test_statistics_of_many_long_rows():
         sigma = (x - mean).square().mean().sqrt()
         assert abs(stats[r, 0] - mean) <= 1e-12 * mean
         assert abs(stats[r, 1] - sigma) <= 1e-12 * sigma
+
+
+@pytest.mark.parametrize("rows", [3, 5000])
+@pytest.mark.parametrize("n_r", [100, 4096, 4100, 8192, 12292])
+def test_statistics_around_whole_tiles(rows, n_r):
+    """Rows of no, one, two and three whole tiles of 4096 points, with and without a remainder: few
+    rows (a chunk per tile) and many (one chunk per row)."""
+    import torch
+    dev = device()
+    g = torch.Generator(device=dev)
+    g.manual_seed(n_r)
+    plane = torch.empty((rows, n_r), dtype=torch.float32, device=dev).exponential_(generator=g) + 3.0
+    stats = torch.empty((rows, 2), dtype=torch.float64, device=dev)
+    J.plane_stats(plane, stats)
+    torch.cuda.synchronize()
+    x = plane.double()
+    mean = x.mean(dim=1)
+    sigma = (x - mean[:, None]).square().mean(dim=1).sqrt()
+    assert ((stats[:, 0] - mean).abs() <= 1e-12 * mean).all()
+    assert ((stats[:, 1] - sigma).abs() <= 1e-12 * sigma).all()
