@@ -31,13 +31,19 @@ constexpr int64_t kPeakTile = kPeakThreads * kPeakPerThread;  // 1024 points
 constexpr int kPeakTilesPerBlock = 32;                        // a block scans 32768 points of a row
 constexpr int kStage = 2048;                                  // LDS candidate staging slots
 constexpr int kMaxGridY = 65535;
+constexpr int64_t kCacheBytes = int64_t(256) << 20;           // of the last-level cache
 
 typedef float f4vec __attribute__((ext_vector_type(4)));
-// A stored plane is far larger than the caches and the statistics read it once: non-temporal loads
-// stream it at 7.1 TB/s on this device, plain ones at 6.4. (The peak finder reads neighbours out
-// of the cache again: its loads stay plain, non-temporal ones made it 8% slower.)
-__device__ __forceinline__ f4vec nt_load4(const float* p) {
-  return __builtin_nontemporal_load(reinterpret_cast<const f4vec*>(p));
+// Four floats of a 16-byte aligned row. NT, for planes that the last-level cache cannot hold:
+// non-temporal loads stream at 7.1 TB/s on this device, plain ones at 6.4. A plane it holds is left there
+// for the peak finder, which reads it next: statistics and selection of 200 MB 103 us, with non-temporal
+// loads in the statistics 114. (The peak finder reads neighbours out of the cache again: its loads
+// are always plain, non-temporal ones made it 8% slower.)
+template <bool NT>
+__device__ __forceinline__ f4vec load4(const float* p) {
+  const f4vec* const q = reinterpret_cast<const f4vec*>(p);
+  if constexpr (NT) return __builtin_nontemporal_load(q);
+  else return *q;
 }
 
 struct Moments {
@@ -73,8 +79,8 @@ __device__ __forceinline__ Moments shfl_xor_moments(Moments v, int off) {
 // quotient of counts from a table instead of a division per 16 values. Bound by the read: 128 rows
 // of 2^22 points 394 -> 318 us (5.4 -> 6.75 TB/s). Chunks of one tile or less have no next one, and
 // many short rows are bound by latency, where the wider kernel's fewer waves cost more: 20000 rows
-// of 100 points take 53 us, in it 62.
-template <bool VEC, bool STREAM>
+// of 100 points take 53 us, in it 62. NT: see load4.
+template <bool VEC, bool STREAM, bool NT = false>
 __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* __restrict__ plane, int64_t ld,
                                                                    int32_t rows, int64_t n_r, int64_t span,
                                                                    Moments* __restrict__ part) {
@@ -97,7 +103,7 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
       f4vec f[4];
       auto load = [&](int64_t at) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) f[q] = nt_load4(src + at + 4 * (q * kStatThreads + (int)threadIdx.x));
+        for (int q = 0; q < 4; ++q) f[q] = load4<NT>(src + at + 4 * (q * kStatThreads + (int)threadIdx.x));
       };
       if (whole > 0) load(lo);
       for (int32_t i = 0; i < whole; ++i) {
@@ -132,7 +138,7 @@ __global__ void __launch_bounds__(kStatThreads) row_moments_kernel(const float* 
         // element e = 4 (q * 256 + tid) + c of the tile
         const int64_t p0 = base + 4 * ((int64_t)q * kStatThreads + threadIdx.x);
         if (VEC && p0 + 3 < hi) {
-          const f4vec f = STREAM ? nt_load4(src + p0) : *reinterpret_cast<const f4vec*>(src + p0);
+          const f4vec f = load4<NT>(src + p0);
           v[4 * q + 0] = f.x;
           v[4 * q + 1] = f.y;
           v[4 * q + 2] = f.z;
@@ -599,7 +605,10 @@ void plane_stats(const float* plane, int64_t ld, int32_t rows, int64_t n_r, doub
   const int64_t span = (tiles + chunks - 1) / chunks * kStatTile;
   const dim3 grid((unsigned)chunks, (unsigned)(rows < kMaxGridY ? rows : kMaxGridY));
   const bool vec = (reinterpret_cast<uintptr_t>(plane) & 15u) == 0 && ld % 4 == 0;
-  if (vec && span >= 2 * kStatTile)
+  if (vec && span >= 2 * kStatTile && (int64_t)rows * n_r * 4 > kCacheBytes)
+    hipLaunchKernelGGL((row_moments_kernel<true, true, true>), grid, dim3(kStatThreads), 0, stream, plane, ld, rows,
+                       n_r, span, static_cast<Moments*>(ws));
+  else if (vec && span >= 2 * kStatTile)
     hipLaunchKernelGGL((row_moments_kernel<true, true>), grid, dim3(kStatThreads), 0, stream, plane, ld, rows, n_r,
                        span, static_cast<Moments*>(ws));
   else if (vec)
