@@ -135,14 +135,16 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
       j.ld = it.ld;
       j.row_max = it.peaks;
       j.rmax_ld = it.keys_ld;
+      fft_job_tiles(j, seg);  // segments
       jobs.push_back(j);
     }
   }
   if (jobs.empty()) return;
-  fft_balance(jobs.data(), (int)jobs.size(), seg, ept);
+  // (a batch of many jobs keeps the plan's blocks: the caller pays for this on every call)
+  if (jobs.size() <= 16) fft_balance(jobs.data(), (int)jobs.size(), seg, ept);
   for (FftJob& j : jobs) {
     j.tile_begin = total;
-    total += fft_job_tiles(j, seg);
+    total += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
   }
 
   if (!p.batch) p.batch = new BatchCtx();

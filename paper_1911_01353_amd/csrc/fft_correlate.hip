@@ -916,61 +916,27 @@ int64_t fft_job_tiles(FftJob& j, int32_t seg_len) {
   return j.n_seg * n_tb;
 }
 
-// A flat launch runs in rounds of the workgroups the device holds at once, so its time is about
-// rounds x (templates per workgroup + the forward transform, worth about 1.5 templates). Large
-// blocks amortise the forward transform, but leave a last round nearly empty, or a small launch short
-// of workgroups; the default rule of the plan, which sees one group alone, knows neither. Of the
-// block sizes up to 64, shared out evenly over each job's templates, the one with the least such
-// time is taken where it gains clearly: a 238-template group of 2^20 bins in one candidate pass (4440 one-wave workgroups
-// of 64 templates on 2048 places: 2.2 rounds) and its neighbours 2.62 -> 2.46 ms, the FDAS search of
-// 201 templates over 2^20 bins (4 a workgroup by default) 681 -> 615 us.
-void fft_balance(FftJob* jobs, int n, int32_t seg_len, int32_t ept) {
-  constexpr double kForward = 1.5;
-  bool any = false;
-  for (int i = 0; i < n; ++i) any = any || (jobs[i].tpb_auto && jobs[i].m_end > jobs[i].m_begin);
+int64_t fft_places(int32_t seg_len, int32_t ept) {
   // measured on the default variant only: the others are asked for by segment length
-  if (!any || seg_len != 1024 || ept != 16) return;
+  if (seg_len != 1024 || ept != 16) return 0;
   int dev = 0, cus = 0;
   JERK_HIP_CHECK(hipGetDevice(&dev));
   JERK_HIP_CHECK(hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev));
-  const double places = (double)std::max(1, cus) * 4 * 2;  // one-wave workgroups, two to a SIMD
-  auto shared_out = [](const FftJob& j, int32_t tpb) {
-    const int32_t m = j.m_end - j.m_begin, blocks = (m + tpb - 1) / tpb;
-    return (m + blocks - 1) / blocks;
-  };
-  // estimated time with blocks of tpb templates (0: the jobs' own), in templates; 0: not possible
-  auto estimate = [&](int32_t tpb, double* tiles_out) {
-    double work = 0.0, tiles = 0.0, most = 0.0;
-    for (int i = 0; i < n; ++i) {
-      FftJob j = jobs[i];
-      if (j.m_end <= j.m_begin || j.nbins <= 0) continue;
-      if (tpb > 0 && j.tpb_auto) j.tpb = shared_out(j, tpb);
-      const double t = (double)fft_job_tiles(j, seg_len), m = j.m_end - j.m_begin;
-      const double cost = std::min((double)j.tpb, m) + kForward;
-      tiles += t;
-      // a job's last block may be short: alone it saves no round, among other jobs' blocks it does
-      work += n == 1 ? t * cost : (double)j.n_seg * m + t * kForward;
-      most = std::max(most, cost);
-    }
-    *tiles_out = tiles;
-    return most > 0.0 ? std::ceil(work / (places * most)) * most : 0.0;
-  };
-  double tiles = 0.0;
-  const double own = estimate(0, &tiles);
-  if (tiles <= places) return;  // one round: the plan's rule spreads it over the device
-  int32_t best = 0;
-  double best_time = 0.93 * own;  // the estimate is rough: a smaller gain is none
-  for (int32_t tpb : {64, 56, 48, 40, 32, 28, 24, 20, 16, 14, 12, 10, 8, 7, 6, 5, 4, 3, 2}) {
-    const double time = estimate(tpb, &tiles);
-    if (tiles >= 2147483648.0) break;  // smaller blocks only add workgroups
-    if (time < (best == 0 ? 1.0 : 0.98) * best_time) {
-      best = tpb;
-      best_time = time;
-    }
+  return (int64_t)std::max(1, cus) * 4 * 2;  // one-wave workgroups, two to a SIMD
+}
+
+void fft_balance(FftJob* jobs, int n, int32_t seg_len, int32_t ept) {
+  bool any = false;
+  for (int i = 0; i < n; ++i) any = any || jobs[i].tpb_auto;
+  const int64_t places = any ? fft_places(seg_len, ept) : 0;
+  if (places == 0) return;
+  std::vector<BalanceRun> runs((size_t)n);
+  for (int i = 0; i < n; ++i) {
+    fft_job_tiles(jobs[i], seg_len);
+    runs[i] = BalanceRun{jobs[i].n_seg, jobs[i].m_end - jobs[i].m_begin, jobs[i].tpb, jobs[i].tpb_auto != 0};
   }
-  if (best == 0) return;
-  for (int i = 0; i < n; ++i)
-    if (jobs[i].tpb_auto && jobs[i].m_end > jobs[i].m_begin) jobs[i].tpb = shared_out(jobs[i], best);
+  balance_blocks(runs.data(), n, places, kMaxTiles, true);
+  for (int i = 0; i < n; ++i) jobs[i].tpb = runs[i].tpb;
 }
 
 // Kernel variants: segment length x elements per thread (16: three radix-16

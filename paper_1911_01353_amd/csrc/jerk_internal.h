@@ -10,6 +10,7 @@
 #include <hip/hip_runtime.h>
 
 #include "../../include/jerk.h"
+#include "balance.h"
 
 namespace jerk {
 
@@ -183,8 +184,11 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
                        int64_t capacity, unsigned long long* d_count, int64_t staged, void* d_ws, size_t ws_bytes,
                        hipStream_t stream);
 
-// Shares the templates of the jobs of one flat launch (those with tpb_auto) out over workgroups
-// again, by the size of the launch. Only speed depends on it.
+constexpr int64_t kMaxTiles = (int64_t(1) << 31) - 1;  // workgroups of one launch
+// Workgroups of a flat launch that the device holds at once, for the variant whose launches share their
+// templates out by their size (balance_blocks); 0: this variant's do not.
+int64_t fft_places(int32_t seg_len, int32_t ept);
+// balance_blocks for the jobs of one flat launch.
 void fft_balance(FftJob* jobs, int n, int32_t seg_len, int32_t ept);
 // Sets j.n_seg and returns the job's tile count (segments x template blocks).
 int64_t fft_job_tiles(FftJob& j, int32_t seg_len);
