@@ -146,3 +146,42 @@ def test_choice_costs_the_caller_little(lib, whole):
             best = min(best, time.perf_counter() - t)
         most = max(most, best)
     assert most < 20e-6, most
+
+
+def as_runs(items):
+    """A batch as the library gives it: few jobs each by itself, of many those of all spectra but the
+    last together per width group."""
+    jobs = [r for item in items for r in item]
+    if len(jobs) <= 16:
+        return copy(jobs)
+    per = len(items[0])
+    head = [Run(sum(i[g].segs for i in items[:-1]), items[0][g].members, items[0][g].tpb, True) for g in range(per)]
+    return copy(head + list(items[-1]))
+
+
+def test_choice_for_batches(lib):
+    """Batches of 2 to 150 uneven spectra: where the blocks change, the launch, whose tiles come
+    spectrum by spectrum, ends earlier."""
+    rng = random.Random(5)
+    changed, gain = 0, []
+    for k in range(150):
+        one = launch(rng)
+        items = []
+        for _ in range(int(2 ** rng.uniform(1, 7.2))):
+            share = rng.uniform(0.25, 1.0)
+            items.append([Run(max(1, int(r.segs * share)), r.members, r.tpb, True) for r in one])
+        runs = as_runs(items)
+        before = [r.tpb for r in runs]
+        per = len(one)
+        lib.choose(runs, len(runs), PLACES, (1 << 31) - 1, per * len(items) <= 16)
+        new = [r.tpb for r in runs][-per:]
+        assert [r.tpb for r in runs] == new * (len(runs) // per)
+        if [r.tpb for r in runs] == before:
+            continue
+        changed += 1
+        own = copy([r for item in items for r in item])
+        got = copy([Run(r.segs, r.members, t, True) for item in items for r, t in zip(item, new)])
+        a, b = lib.finish(own, len(own), PLACES), lib.finish(got, len(got), PLACES)  # every tile in order
+        assert b < a, (k, len(items), [(r.segs, r.members, r.tpb) for r in one], new, a, b)
+        gain.append(a / b)
+    assert changed > 30 and max(gain) > 1.1
