@@ -2,6 +2,7 @@
 #include "balance.h"
 
 #include <algorithm>
+#include <cmath>
 #include <limits>
 #include <vector>
 
@@ -119,6 +120,15 @@ void balance_blocks(BalanceRun* runs, int n, int64_t places, int64_t max_tiles, 
   if (size == 0) return;
   for (int i = 0; i < n; ++i)
     if (runs[i].free && runs[i].members > 0) runs[i].tpb = shared_out(runs[i].members, size);
+}
+
+// The filter of a candidate pass reads a tile's hits one after the other, a thread per tile, at about
+// 0.3 us a hit. Larger tiles hold more of them: with the staging level at 2 mean powers, blocks of 16
+// templates grown to 28 and 60 made the filter most of the search (765 templates over 2^18 bins 5.2 -> 10.2 ms),
+// at 5.4 mean powers they took 1.82 ms instead of 1.50. So only where a larger tile expects at most 16 hits
+// (5 us; at the usual levels above 11 mean powers it expects one or two).
+bool candidate_blocks_allowed(int32_t tpb, int32_t own, int32_t U, double pre) {
+  return tpb <= own || 2.0 * (double)tpb * (double)U * std::exp(-std::max(0.0, pre)) <= 16.0;
 }
 
 }  // namespace jerk

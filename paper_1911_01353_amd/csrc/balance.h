@@ -24,4 +24,8 @@ double dispatch_time(const BalanceRun* runs, int n, int64_t places, double limit
 // for several jobs whose tiles are mixed. Never more than max_tiles tiles. Only speed depends on it.
 void balance_blocks(BalanceRun* runs, int n, int64_t places, int64_t max_tiles, bool whole);
 
+// Whether a candidate pass, whose staged hits are read back tile by tile, may take blocks of `tpb`
+// templates instead of the plan's `own`. U: lags of a segment, pre: the staging level.
+bool candidate_blocks_allowed(int32_t tpb, int32_t own, int32_t U, double pre);
+
 }  // namespace jerk

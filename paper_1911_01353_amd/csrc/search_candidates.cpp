@@ -214,8 +214,9 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
     size_t hit_counts = L.hits - L.tile_hits;  // bytes of the tiles' hit counts, the slots behind them
     j.tpb = g.tpb;
     if (g.tpb_auto && staged <= 0) {
-      // Other blocks where the launch gains by them (fft_balance) and the space the layout has for
-      // g.tpb still gives each tile twice its expected hits and four.
+      // Other blocks where the launch gains by them (fft_balance), reading back the hits does not lose
+      // it again, and the space the layout has for g.tpb still gives each tile twice its expected hits
+      // and four.
       FftJob b = j;
       b.tpb_auto = 1;
       fft_balance(&b, 1, g.seg_len, g.ept);
@@ -227,7 +228,7 @@ void search_candidates(const Plan& p, const void* d_bank, const void* d_spec, in
       const size_t counts = align_up((size_t)b_tiles * sizeof(uint32_t)), space = L.pool - L.tile_hits;
       const int64_t full = group_cap(bg, pre, 0);
       const int64_t slots = space > counts ? (int64_t)((space - counts) / sizeof(CandHit)) / b_tiles : 0;
-      if (b_tiles < (int64_t(1) << 31) && slots >= full - 12) {
+      if (candidate_blocks_allowed(b.tpb, g.tpb, U, pre) && b_tiles < (int64_t(1) << 31) && slots >= full - 12) {
         j.tpb = b.tpb;
         tiles = b_tiles;
         cap = (int32_t)std::min(full, slots);

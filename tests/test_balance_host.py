@@ -31,7 +31,9 @@ def lib(tmp_path_factory):
                    'extern "C" void choose(jerk::BalanceRun* r, int n, int64_t places, int64_t most, bool in_order) {\n'
                    '  jerk::balance_blocks(r, n, places, most, in_order);\n}\n'
                    'extern "C" double finish(const jerk::BalanceRun* r, int n, int64_t places) {\n'
-                   '  return jerk::dispatch_time(r, n, places, 1e300);\n}\n')
+                   '  return jerk::dispatch_time(r, n, places, 1e300);\n}\n'
+                   'extern "C" bool allowed(int32_t tpb, int32_t own, int32_t U, double pre) {\n'
+                   '  return jerk::candidate_blocks_allowed(tpb, own, U, pre);\n}\n')
     so = d / "libbalance.so"
     subprocess.run(["g++", "-O2", "-std=c++17", "-shared", "-fPIC", "-I", CSRC, str(src),
                     os.path.join(CSRC, "balance.cpp"), "-o", str(so)], check=True)
@@ -39,6 +41,8 @@ def lib(tmp_path_factory):
     out.choose.argtypes = [ctypes.POINTER(Run), ctypes.c_int, ctypes.c_int64, ctypes.c_int64, ctypes.c_bool]
     out.finish.argtypes = [ctypes.POINTER(Run), ctypes.c_int, ctypes.c_int64]
     out.finish.restype = ctypes.c_double
+    out.allowed.argtypes = [ctypes.c_int32, ctypes.c_int32, ctypes.c_int32, ctypes.c_double]
+    out.allowed.restype = ctypes.c_bool
     return out
 
 
@@ -185,3 +189,12 @@ def test_choice_for_batches(lib):
         assert b < a, (k, len(items), [(r.segs, r.members, r.tpb) for r in one], new, a, b)
         gain.append(a / b)
     assert changed > 30 and max(gain) > 1.1
+
+
+def test_candidate_passes_with_many_hits_keep_their_blocks(lib):
+    """A candidate pass reads a tile's hits back one after the other: blocks grow only where a larger
+    tile expects few."""
+    assert lib.allowed(60, 16, 928, 11.7) and lib.allowed(64, 4, 993, 9.0)
+    for pre in (-1.0, 0.0, 2.0, 5.4, 6.0):
+        assert not lib.allowed(28, 16, 928, pre) and not lib.allowed(9, 4, 928, pre)
+        assert lib.allowed(16, 16, 928, pre) and lib.allowed(8, 16, 928, pre)
