@@ -140,28 +140,6 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
     }
   }
   if (jobs.empty()) return;
-  if (const int64_t places = fft_places(seg, ept)) {
-    // Few jobs each by itself. Of many, those of all spectra but the last together per width group
-    // (they have the same templates) and the last spectrum's, whose tiles end the launch, by
-    // themselves: the caller pays for this on every call, and job by job it took half as long as the
-    // rest of the call (256 spectra of 2^12 bins, 24 templates: 428 us a call, now 276)
-    const size_t per = jobs.size() / (size_t)count, last = jobs.size() - per;  // every spectrum's jobs
-    const bool each = jobs.size() <= 16;
-    auto run_of = [&](size_t i) { return each ? i : i < last ? i % per : per + i - last; };
-    std::vector<BalanceRun> runs(each ? jobs.size() : 2 * per, BalanceRun{0, 0, 1, false});
-    for (size_t i = 0; i < jobs.size(); ++i) {
-      const FftJob& j = jobs[i];
-      BalanceRun& r = runs[run_of(i)];
-      r = BalanceRun{r.segs + j.n_seg, j.m_end - j.m_begin, j.tpb, j.tpb_auto != 0};
-    }
-    balance_blocks(runs.data(), (int)runs.size(), places, kMaxTiles, each);
-    for (size_t i = 0; i < jobs.size(); ++i) jobs[i].tpb = runs[run_of(i)].tpb;
-  }
-  for (FftJob& j : jobs) {
-    j.tile_begin = total;
-    total += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
-  }
-
   if (!p.batch) p.batch = new BatchCtx();
   BatchCtx& c = *p.batch;
   std::lock_guard<std::mutex> lock(c.mu);
@@ -180,6 +158,36 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
     c.grid_cache_seg = seg;
     c.grid_cache_ept = ept;
   }
+  if (int64_t places = fft_places(seg, ept)) {
+    // the persistent kernel's workgroups take tiles in the same order, but it holds fewer of them, and
+    // they share one counter: never more tiles than with the plan's blocks
+    int64_t most = kMaxTiles;
+    if (!flat) {
+      places = c.grid_cache;
+      most = 0;
+      for (const FftJob& j : jobs) most += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
+    }
+    // Few jobs each by itself. Of many, those of all spectra but the last together per width group
+    // (they have the same templates) and the last spectrum's, whose tiles end the launch, by
+    // themselves: the caller pays for this on every call, and job by job it took half as long as the
+    // rest of the call (256 spectra of 2^12 bins, 24 templates: 428 us a call, now 276)
+    const size_t per = jobs.size() / (size_t)count, last = jobs.size() - per;  // every spectrum's jobs
+    const bool each = jobs.size() <= 16;
+    auto run_of = [&](size_t i) { return each ? i : i < last ? i % per : per + i - last; };
+    std::vector<BalanceRun> runs(each ? jobs.size() : 2 * per, BalanceRun{0, 0, 1, false});
+    for (size_t i = 0; i < jobs.size(); ++i) {
+      const FftJob& j = jobs[i];
+      BalanceRun& r = runs[run_of(i)];
+      r = BalanceRun{r.segs + j.n_seg, j.m_end - j.m_begin, j.tpb, j.tpb_auto != 0};
+    }
+    balance_blocks(runs.data(), (int)runs.size(), places, most, each);
+    for (size_t i = 0; i < jobs.size(); ++i) jobs[i].tpb = runs[run_of(i)].tpb;
+  }
+  for (FftJob& j : jobs) {
+    j.tile_begin = total;
+    total += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
+  }
+
   const int32_t grid = (int32_t)std::min<int64_t>(c.grid_cache, total);
 
   // Stage header + jobs. The staging buffer is reused: wait for the previous copy.
