@@ -65,6 +65,19 @@ std::pair<int32_t, int32_t> uniform_variant(const Plan& p) {
   return {s, e};
 }
 
+// Tiles a workgroup of the persistent kernel takes from the counter at a time. The counter gives one
+// about every 4.5 ns, which small tiles of segments up to 1024 points wait for: those go in runs of
+// about 24 templates, but at most an eighth of a workgroup's share of the launch (longer runs leave a
+// longer end). 64 spectra of 2^20 to 2^22 bins, 512-point segments in blocks of 8: 2.23 s a pass tile by
+// tile, 1.43 s in runs, 1.46 s in flat launches.
+int32_t persistent_run(const std::vector<FftJob>& jobs, int64_t total, int32_t grid, int32_t seg) {
+  if (seg > 1024) return 1;
+  double templates = 0.0;
+  for (const FftJob& j : jobs) templates += (double)j.n_seg * (double)(j.m_end - j.m_begin);
+  const int64_t run = (int64_t)(24.0 * (double)total / std::max(1.0, templates));
+  return (int32_t)std::max<int64_t>(1, std::min(run, total / (8 * (int64_t)grid)));
+}
+
 }  // namespace
 
 size_t batch_workspace_bytes(const Plan& p, int32_t count) { return jobs_capacity_bytes(p, count); }
@@ -204,6 +217,7 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
   h.total_tiles = total;
   h.counter = 0;
   h.n_jobs = (int32_t)jobs.size();
+  h.run = flat ? 1 : persistent_run(jobs, total, grid, seg);
   std::memset(c.pinned, 0, kHeaderBytes);
   std::memcpy(c.pinned, &h, sizeof(h));
   std::memcpy(static_cast<char*>(c.pinned) + kHeaderBytes, jobs.data(), jobs.size() * sizeof(FftJob));

@@ -785,9 +785,12 @@ __global__ void __launch_bounds__(S / E, (min_waves<S, E, R4>())) fft_correlate_
   fft_tile<S, E, R1, R2, R3, R4, KEYS>(j, blk % j.n_seg, m0, min(m0 + j.tpb, j.m_end), lds, red, tw);
 }
 
-// Persistent launch over a job table: every workgroup takes tiles from a
-// device counter until all tiles of all jobs are done (every workgroup
-// reaches the exit test). Tile i belongs to the job whose [tile_begin,
+// Persistent launch over a job table: every workgroup starts with the run of
+// tiles of its index and takes further runs from a device counter until all
+// tiles of all jobs are done (the counter only grows, so every workgroup
+// reaches the exit test). Without the first run dealt out, the workgroups
+// queued for the counter at once: two spectra of 10^5 bins, 40 templates in
+// 512-point segments 124 -> 79 us. Tile i belongs to the job whose [tile_begin,
 // next tile_begin) holds it; within a job, tile = tb * n_seg + seg.
 template <int S, int E, int R1, int R2, int R3, int R4, bool KEYS>
 __global__ void __launch_bounds__(S / E) fft_persistent_kernel(const FftJob* __restrict__ jobs,
@@ -798,12 +801,9 @@ __global__ void __launch_bounds__(S / E) fft_persistent_kernel(const FftJob* __r
   __shared__ int64_t s_tile;
   const int64_t total = hdr->total_tiles;
   const int n_jobs = hdr->n_jobs;
-  for (;;) {
-    if (threadIdx.x == 0) s_tile = (int64_t)atomicAdd(&hdr->counter, 1ull);
-    __syncthreads();
-    const int64_t tile = s_tile;
-    __syncthreads();
-    if (tile >= total) break;
+  const int64_t run = max(1, hdr->run), dealt = (int64_t)gridDim.x * run;
+  int64_t tile = (int64_t)blockIdx.x * run, end = min(tile + run, total);  // of the run at hand
+  while (tile < total) {
     int lo = 0, hi = n_jobs - 1;  // last job with tile_begin <= tile
     while (lo < hi) {
       const int mid = (lo + hi + 1) >> 1;
@@ -822,6 +822,13 @@ __global__ void __launch_bounds__(S / E) fft_persistent_kernel(const FftJob* __r
     const float2* twt = (const float2*)twg;
     const int m0 = j.m_begin + (int)(local / j.n_seg) * j.tpb;
     fft_tile<S, E, R1, R2, R3, R4, KEYS, 0, true>(j, local % j.n_seg, m0, min(m0 + j.tpb, j.m_end), lds, red, twt);
+    __syncthreads();  // the tile's use of LDS
+    if (++tile == end) {
+      if (threadIdx.x == 0) s_tile = dealt + (int64_t)atomicAdd(&hdr->counter, (unsigned long long)run);
+      __syncthreads();
+      tile = s_tile;
+      end = min(tile + run, total);
+    }
   }
 }
 

@@ -116,7 +116,7 @@ struct BatchHeader {
   int64_t total_tiles;
   unsigned long long counter;
   int32_t n_jobs;
-  int32_t pad;
+  int32_t run;  // tiles a workgroup of the persistent kernel takes at a time
 };
 // Candidate selection fused into the FFT path (search_candidates.cpp). Rows are the
 // members [lo, hi) of one width group's member list, row r = member lo + r.

@@ -205,3 +205,23 @@ def test_batch_full_size_matches_single_searches(flat):
             del ref
         del planes, keys
     plan.close()
+
+
+@pytest.mark.parametrize("seg", [512, 1024])
+@pytest.mark.parametrize("graph", [False, True])
+def test_persistent_runs_of_tiles_match_flat(seg, graph):
+    """Enough small tiles that a workgroup of the persistent kernel takes several at a time (16 tiles and
+    more a workgroup, blocks of 4): planes and keys equal the flat launch's, run after run, with a
+    last run cut short and spectra of one segment among them."""
+    device()
+    plan = J.Plan(1 << 18, 20.0, 60.0, 2.0, 20.0, path="fft", seg_len=seg, templates_per_block=4)
+    bank = build_bank(plan)
+    T = plan.info()["n_templates"]
+    specs = _spectra([(1 << 18) + 3, 1, (1 << 18) - 1001, 200, 250007, 240001], 21)
+    want = _run_batch(plan, bank, specs, False, 0, T, flat=True)
+    for _ in range(2):
+        got = _run_batch(plan, bank, specs, graph, 0, T, flat=False)
+        for (a, pa), (b, pb) in zip(got, want):
+            assert np.array_equal(a.view(np.uint32), b.view(np.uint32))
+            assert np.array_equal(pa[0], pb[0]) and np.array_equal(pa[1], pb[1])
+    plan.close()
