@@ -134,3 +134,45 @@ def test_wide_fp16_groups_share_launches(n):
     assert np.array_equal(got["p"].astype(np.int64), plane.argmax(axis=1))
     assert np.array_equal(got["power"], plane.max(axis=1))
     plan.close()
+
+
+@pytest.fixture(scope="module")
+def long_spectrum():
+    return _spec((1 << 21) + 77, 64)
+
+
+@pytest.mark.parametrize("taps", list(range(16, 257, 16)))
+def test_fp16_several_windows_per_wave(long_spectrum, taps):
+    """Every FP16 tap count on a spectrum long enough that a wave takes several windows (16 templates,
+    at least 4 windows each): points at the ends of windows, at both ends of the spectrum and at random
+    against the FP64 correlation with the bank's taps, row peaks against the plane's."""
+    import torch
+    from gpu_helpers import bank_taps
+    dev = device()
+    n = long_spectrum.shape[0]
+    plan = J.Plan(n, 15.0, 0.0, 2.0, 20.0, path="fp16", margin=taps // 2 - 8, tap_quantum=taps)
+    assert [(g["taps"], g["n_members"]) for g in plan.groups()] == [(taps, 16)]
+    bank = build_bank(plan)
+    spec = torch.from_numpy(long_spectrum).to(dev)
+    plane = torch.full((16, 2 * n), float("nan"), dtype=torch.float32, device=dev)
+    plan.search(bank, spec, plane)
+    torch.cuda.synchronize()
+    assert not torch.isnan(plane).any()
+    rng = np.random.default_rng(taps)
+    edges = np.concatenate([[w * 64 - 1, w * 64] for w in (*range(1, 40), *rng.integers(40, n // 64, 60))])
+    at = np.unique(np.concatenate([[0, 1, n - 2, n - 1], edges, rng.integers(0, n, 100)]))
+    hg = taps // 2
+    x = np.concatenate([np.zeros(hg - 1), long_spectrum.astype(np.complex128), np.zeros(hg)])
+    window = x[at[:, None] + np.arange(taps)[None, :]]  # (points, taps): tap j takes bin k0 - hg + 1 + j
+    coef = bank_taps(plan, bank, 0)
+    got = plane.cpu().numpy()
+    for k, t in enumerate(plan.members()):
+        for phase in (0, 1):
+            want = np.abs(window @ coef[k, phase]) ** 2
+            err = np.abs(got[t, 2 * at + phase] - want) / np.maximum(want, got[t].mean(dtype=np.float64))
+            assert err.max() <= 1e-2, (t, phase, err.max())
+    peaks = J.peaks_numpy(plan.search_peaks(bank, spec), 16)
+    torch.cuda.synchronize()
+    assert np.array_equal(peaks["p"].astype(np.int64), got.argmax(axis=1))
+    assert np.array_equal(peaks["power"], got.max(axis=1))
+    plan.close()

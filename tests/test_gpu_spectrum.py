@@ -79,3 +79,13 @@ def test_pass_plans(log_n):
     rng = np.random.default_rng(log_n)
     x = rng.standard_normal(1 << log_n).astype(np.float32)
     _compare(_gpu_spectrum(x), prepare_spectrum(x))
+
+
+@pytest.mark.parametrize("log_n", [13, 16, 18, 19, 21, 22, 23, 24])
+def test_every_radix_of_the_passes(log_n):
+    """2^12 to 2^23 bins: passes of radix 32 (2^12), 256 (2^15), 32 and 32 (2^17), 64 and 32 (2^18),
+    128 and 64 (2^20), 128 and 128 (2^21), 256 and 128 (2^22), 256 and 256 (2^23, the largest whose
+    partial sums are not folded) before the last one."""
+    rng = np.random.default_rng(log_n)
+    x = rng.standard_normal(1 << log_n).astype(np.float32)
+    _compare(_gpu_spectrum(x), prepare_spectrum(x))
