@@ -90,8 +90,9 @@ typedef struct jerk_plan_desc {
   int32_t templates_per_block; /* FFT path templates per workgroup (1..64), or 0: per group the
                                   largest of 64, 32, 16, 8 whose launch over the whole group
                                   has 4096 workgroups at nbins, else 4; a launch larger than
-                                  the device holds at once may then share its templates out
-                                  otherwise (results do not depend on it)                   */
+                                  the device holds at once (not the request server's) may
+                                  then share its templates out otherwise (results do not
+                                  depend on it)                                           */
   int32_t tap_quantum;         /* width-group granularity in taps (16..512, mult of 16) or 0 */
   uint32_t flags;              /* reserved, must be 0                                  */
 } jerk_plan_desc;
@@ -111,7 +112,8 @@ typedef struct jerk_plan_info_t {
 typedef struct jerk_group_info_t {
   int32_t taps;                /* K_g: taps of every template of the group (even)        */
   int32_t seg_len;             /* FFT segment length S_g                                */
-  int32_t templates_per_block; /* FFT path templates per workgroup                      */
+  int32_t templates_per_block; /* FFT path templates per workgroup (of the plan: see
+                                  jerk_plan_desc for launches of a plan with the default)  */
   int32_t path;                /* resolved path (FFT_FP32, GEMM_SPLIT_BF16 or GEMM_FP16) */
   int32_t n_members;           /* templates in the group                                */
   int32_t first_member;        /* index of its first entry in jerk_plan_members order   */
@@ -136,7 +138,9 @@ int32_t jerk_plan_template(const jerk_plan* plan, int32_t t, double* zbar, doubl
 int32_t jerk_plan_members(const jerk_plan* plan, int32_t* out, int32_t count);
 /* Overrides one group's FFT segment length, templates per block, path and FFT kernel variant
  * (fft_ept: complex elements per thread, 8 or 16; 0 = default) before jerk_templates_build
- * (used by the autotuner). Changes bank_bytes; EINVAL if out of range. */
+ * (used by the autotuner). Changes bank_bytes; EINVAL if out of range. The group's launches then
+ * keep these templates per block whatever their size, also where they equal the default (so a plan
+ * with the default that is written out and set again gives the same results from other launches). */
 int32_t jerk_plan_set_group(jerk_plan* plan, int32_t g, int32_t seg_len,
                             int32_t templates_per_block, int32_t path, int32_t fft_ept);
 

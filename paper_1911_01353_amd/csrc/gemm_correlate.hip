@@ -754,7 +754,7 @@ void gemm_correlate_launch(const GemmArgs& a, hipStream_t stream) {
   const bool split = a.path != JERK_PATH_GEMM_FP16;
   // One row block (8 templates) per wave; the tap fragments of up to 128 taps
   // (split) or 256 taps (FP16) stay in registers across windows.
-  // window = 64 outputs + taps + 8 slack elements, loaded 64 per lane-step
+  // window = 128 or 64 outputs (window_cols) + taps + 8 slack elements, loaded 64 per lane-step
   if (a.row_max) {
     // peak-key launches keep one row block per wave (room for the per-row keys)
     if (split) {

@@ -290,7 +290,8 @@ void make_units(jerk_server& s, Req* q, int64_t target) {
         q->units.push_back({gi, m, e, n_seg * ((e - m + g.tpb - 1) / g.tpb)});
       }
     } else {
-      // MFMA units: 32 templates (4 row blocks); tile estimate = row blocks x 64-output windows / 8
+      // MFMA units: 32 templates (4 row blocks); estimate of their work = row blocks x bins / 512 (the
+      // kernels' windows, of 64 or 128 outputs by tap count, do not matter to it)
       const int64_t n_win = (q->r.nbins + 63) / 64;
       const int32_t step = 32;
       for (int32_t m = 0; m < n; m += step) {

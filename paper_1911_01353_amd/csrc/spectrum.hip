@@ -337,17 +337,19 @@ __global__ void __launch_bounds__(kSmallMax / 4) small_spectrum_kernel(const flo
 }
 
 struct WsLayout {
-  size_t a, b, part, scale, total;
+  size_t a, b, part, fold, total;
 };
+
+int64_t last_pass_blocks(int64_t M) { return M / kPoints; }  // kLastCols columns and their mirrors each
 
 WsLayout ws_layout(int64_t M) {
   WsLayout w{};
-  const int64_t blocks = (M + kThreads - 1) / kThreads;
   w.a = 0;
   w.b = align_up((size_t)M * sizeof(double2));
-  w.part = w.b + align_up((size_t)M * sizeof(double2));
-  w.scale = w.part + align_up((size_t)blocks * sizeof(double));
-  w.total = w.scale + kAlign;
+  w.part = w.b + align_up((size_t)M * sizeof(double2));               // last_pass_blocks sums
+  w.fold = w.part + align_up((size_t)last_pass_blocks(M) * sizeof(double));  // kMaxParts of them, if there are more
+  // one sum per kThreads points and a value: the size callers have been told, more than both take
+  w.total = w.part + align_up((size_t)((M + kThreads - 1) / kThreads) * sizeof(double)) + kAlign;
   return w;
 }
 
@@ -404,15 +406,16 @@ void spectrum_prepare(const float* series, int64_t n_samples, float2* spec, void
     rest -= bits;
   }
   double2* X = buf[cur];
-  int64_t nparts = (M / kLastRadix) / (2 * kLastCols);
+  int64_t nparts = last_pass_blocks(M);
   hipLaunchKernelGGL(last_pass_kernel, dim3((unsigned)nparts), dim3(kThreads), 0, stream,
                      static_cast<const double2*>(in), M, X, part);
   JERK_HIP_CHECK(hipGetLastError());
   if (nparts > kMaxParts) {  // M > 2^23
-    hipLaunchKernelGGL(fold_parts_kernel, dim3((unsigned)kMaxParts), dim3(kThreads), 0, stream, part, nparts,
-                       part + nparts);
+    double* const folded = reinterpret_cast<double*>(base + w.fold);
+    require(w.fold + (size_t)kMaxParts * sizeof(double) <= w.total, JERK_EINTERNAL, "folded sums outside the workspace");
+    hipLaunchKernelGGL(fold_parts_kernel, dim3((unsigned)kMaxParts), dim3(kThreads), 0, stream, part, nparts, folded);
     JERK_HIP_CHECK(hipGetLastError());
-    part += nparts;
+    part = folded;
     nparts = kMaxParts;
   }
   const int64_t blocks = M / 1024;
