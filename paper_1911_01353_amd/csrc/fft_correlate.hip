@@ -676,10 +676,10 @@ __device__ __forceinline__ void fft_tile(const FftJob& j, int64_t seg, int m0, i
     // loads are issued one whole stage of the other phase (about 200 VALU instructions) before
     // their use; the next template's spectra load during this template's last stages. With one
     // phase after the other, waves spent 33% of their cycles waiting on LDS and memory counters
-    // (1024 points, row peaks of 2^20 bins x 765 templates); now 16%. With the twiddles folded into
-    // the butterflies (DftTw) that search went from 2.20 to 1.92 ms, the 2^22-bin plane slab of 201
-    // templates from 2.52 to 2.34 ms (the clock drops to 1.75 GHz while the plane is written), the
-    // 2^15-bin search from 26.1 to 21.4 us.
+    // (1024 points, row peaks of 2^20 bins x 765 templates); now 20%. With the twiddles folded into
+    // the butterflies (DftTw) that search went from 2.20 to 1.90 ms, the 2^22-bin plane slab of 201
+    // templates from 2.53 to 2.36 ms (GRBM_GUI_ACTIVE over kernel time: 2.1 GHz for the row peaks, 1.7 to
+    // 1.9 while the plane is written), the 2^15-bin search from 26.1 to 21.4 us.
     auto fence = [] {
       asm volatile("" ::: "memory");
       __builtin_amdgcn_sched_barrier(0);
