@@ -469,7 +469,7 @@ gemm_correlate_mw_kernel(GemmArgs a, int64_t windows_per_wg, int64_t n_colchunks
 // k-step instead of one per column tile) and no tap count is checked in the loops; 128 outputs per
 // window. One body for all tap counts with 64 outputs per window read two fragments per two MFMAs,
 // which is all the LDS delivers; 303 templates of 32 to 144 taps over 2^20 bins: 968 -> 707 us
-// (3.6 TB/s written; MFMA 36% busy, bound by the stores and their power). Tap counts of these
+// (3.6 TB/s written; MFMA 36% busy; bound by the stores beside the products). Tap counts of these
 // kernels, their k-step slots (two runs of
 // ceil(K / 32) per part) and the loads of a 128-output window per lane.
 #define JERK_FP16_NARROW_TAPS(X) X(16) X(32) X(48) X(64) X(80) X(96) X(112) X(128)
