@@ -174,18 +174,18 @@ void batch_search(Plan& p, const void* d_bank, const jerk_batch_item* items, int
   if (int64_t places = fft_places(seg, ept)) {
     // the persistent kernel's workgroups take tiles in the same order, but it holds fewer of them, and
     // they share one counter: never more tiles than with the plan's blocks
-    int64_t most = kMaxTiles;
-    if (!flat) {
-      places = c.grid_cache;
-      most = 0;
-      for (const FftJob& j : jobs) most += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
-    }
-    // Few jobs each by itself. Of many, those of all spectra but the last together per width group
-    // (they have the same templates) and the last spectrum's, whose tiles end the launch, by
-    // themselves: the caller pays for this on every call, and job by job it took half as long as the
-    // rest of the call (256 spectra of 2^12 bins, 24 templates: 428 us a call, now 276)
+    int64_t tiles = 0;
+    for (const FftJob& j : jobs) tiles += j.n_seg * ((j.m_end - j.m_begin + j.tpb - 1) / j.tpb);
+    const int64_t most = flat ? kMaxTiles : tiles;
+    if (!flat) places = c.grid_cache;
+    // Few jobs each by itself, which costs about 0.35 us a job: up to 16, and up to 32 where two
+    // rounds of tiles last longer than that. Of many, those of all spectra but the last together per
+    // width group (they have the same templates) and the last spectrum's, whose tiles end the launch,
+    // by themselves: the caller pays for this on every call, and job by job it took half as long as
+    // the rest of the call (256 spectra of 2^12 bins, 24 templates: 428 us a call, now 276). Six
+    // spectra of 271425 bins, 26 templates (18 jobs): 139 us together, 125 each by itself.
     const size_t per = jobs.size() / (size_t)count, last = jobs.size() - per;  // every spectrum's jobs
-    const bool each = jobs.size() <= 16;
+    const bool each = jobs.size() <= 16 || (jobs.size() <= 32 && tiles >= 2 * places);
     auto run_of = [&](size_t i) { return each ? i : i < last ? i % per : per + i - last; };
     std::vector<BalanceRun> runs(each ? jobs.size() : 2 * per, BalanceRun{0, 0, 1, false});
     for (size_t i = 0; i < jobs.size(); ++i) {

@@ -159,7 +159,7 @@ def as_runs(items):
     """A batch as the library gives it: few jobs each by itself, of many those of all spectra but the
     last together per width group."""
     jobs = [r for item in items for r in item]
-    if len(jobs) <= 16:
+    if len(jobs) <= 16 or (len(jobs) <= 32 and sum(r.segs * -(-r.members // r.tpb) for r in jobs) >= 2 * PLACES):
         return copy(jobs)
     per = len(items[0])
     head = [Run(sum(i[g].segs for i in items[:-1]), items[0][g].members, items[0][g].tpb, True) for g in range(per)]
@@ -180,7 +180,7 @@ def test_choice_for_batches(lib):
         runs = as_runs(items)
         before = [r.tpb for r in runs]
         per = len(one)
-        lib.choose(runs, len(runs), PLACES, (1 << 31) - 1, per * len(items) <= 16)
+        lib.choose(runs, len(runs), PLACES, (1 << 31) - 1, len(runs) == per * len(items))
         new = [r.tpb for r in runs][-per:]
         assert [r.tpb for r in runs] == new * (len(runs) // per)
         if [r.tpb for r in runs] == before:
