@@ -137,8 +137,8 @@ def test_fixed_blocks_and_the_tile_limit_are_kept(lib):
 
 @pytest.mark.parametrize("whole", [False, True])
 def test_choice_costs_the_caller_little(lib, whole):
-    """Every search and batch call pays for the choice: below 20 us for eight jobs (instrumented hosts
-    are not timed)."""
+    """Every search and batch call pays for the choice: under 10 us for eight jobs on the hosts it was
+    written on; ten times that is refused (instrumented hosts are not timed)."""
     if "asan" in os.environ.get("LD_PRELOAD", ""):
         pytest.skip("address sanitizer preloaded")
     rng = random.Random(3)
@@ -146,13 +146,13 @@ def test_choice_costs_the_caller_little(lib, whole):
     for _ in range(40):
         own = launch(rng)
         best = 1.0
-        for _ in range(5):
+        for _ in range(20):
             new = copy(own)
             t = time.perf_counter()
             lib.choose(new, len(new), PLACES, (1 << 31) - 1, whole)
             best = min(best, time.perf_counter() - t)
         most = max(most, best)
-    assert most < 20e-6, most
+    assert most < 100e-6, most
 
 
 def as_runs(items):
